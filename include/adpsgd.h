@@ -197,7 +197,8 @@ typedef struct {
     double gamma;       /* learning rate of step t                                    */
 } adpsgd_step_rec;
 
-/* Per-kernel device time, from HIP events around the sampled launches. */
+/* Per-kernel device time, from HIP events around the sampled launches.  A
+ * launch of several steps counts as that many step launches. */
 typedef struct {
     double step_ms;     int64_t step_launches;     /* plain local step            */
     double fused_ms;    int64_t fused_launches;    /* last step of a period + sync */
@@ -234,6 +235,7 @@ ADPSGD_API int adpsgd_reset(adpsgd_ctx *c);
 
 /* Enqueue n >= 0 plain local steps t .. t+n-1 on every worker (Algorithm 2's
  * update): d = h (x - x*) + sigma z + wd x; m = mu m + d; x = x - gamma_t m.
+ * Up to 64 steps share one launch, which reads and writes x and m once.
  * Advances t and cnt by n; a constant period that switches at p_switch_step
  * (hparams) becomes p_after in the state once a step t >= p_switch_step is
  * taken, as in adpsgd_sched_step.  Asynchronous. */

@@ -41,6 +41,9 @@ struct Chunk {
     int32_t pad_;
 };
 
+// Local steps per launch at most: their rates travel in the kernel arguments.
+constexpr int kSpanSteps = 64;
+
 // Everything a local step needs.  Replicas are rows of x and m, ld elements apart.
 struct StepParams {
     float *x;
@@ -51,18 +54,19 @@ struct StepParams {
     int64_t P;
     int64_t n_groups;  // ceil(P / 4)
     int32_t K;
-    uint32_t t;        // step index (Philox counter word 2)
-    float sigma, mu, wd, gamma;
+    uint32_t t;        // first step's index (Philox counter word 2)
+    float sigma, mu, wd;
+    int32_t n;         // steps of this launch: t .. t + n - 1 (k_local_step; the sync kernels take one)
     RoundKeys rk;
     // Chunks of one worker's row that an XCD takes one after another before
     // the next worker's (the local step's block order; set by
     // launch_local_step, ignored by the sync kernels).
     int32_t row_chunks;
-    int32_t pad_;
     // First block of this launch: a dispatch counts its grid in 32-bit
     // work-items, so larger grids go out as several launches (the launchers
     // below set it; callers leave it 0).
     int64_t block0;
+    float gamma[kSpanSteps];  // the rates of steps t .. t + n - 1
 };
 
 struct SyncParams {
@@ -103,12 +107,17 @@ constexpr int kMaxRowChunks = 4096;
 // The shapes adpsgd_init times: the three block sizes with one chunk per row
 // run, 64-thread blocks held to 20 per CU (8 KB each), and those with runs of
 // 16, 32 and 64 chunks.
+// A launch of n >= kUncappedSteps steps leaves the LDS reservation out: it is
+// bound by arithmetic, not by HBM, and wants every wave it can hold (measured
+// with and without the 8 KB reservation, K = 8, P = 138M: 1 step 2.97 and 3.03
+// ms, 2 steps 3.02 and 3.05, 3 steps 3.16 and 3.10, 4 steps 3.52 and 3.26).
+constexpr int kUncappedSteps = 3;
 constexpr StepShape kStepShapes[] = {{64, 0, 1},     {64, 8192, 1},  {128, 0, 1},   {256, 0, 1},
                                      {64, 8192, 16}, {64, 8192, 32}, {64, 8192, 64}};
 int64_t local_step_blocks(int64_t n_groups, int32_t K, const StepShape &shape);
 // vec: rows are 16-byte aligned (row stride % 4 == 0) so full groups use
 // dwordx4; shape: block one of kStepBlocks, lds in [0, kMaxStepLds],
-// row_chunks in [1, kMaxRowChunks] (hipErrorInvalidValue otherwise).
+// row_chunks in [1, kMaxRowChunks]; p.n in [1, kSpanSteps] (hipErrorInvalidValue otherwise).
 hipError_t launch_local_step(const StepParams &p, bool vec, bool nontemporal, const StepShape &shape,
                              hipStream_t st);
 // What a sync-tile kernel does:

@@ -201,6 +201,7 @@ int hip_fail(hipError_t e, const char *what) {
 struct TimedLaunch {
     int kind;
     hipEvent_t start, stop;
+    int32_t steps;   // launches of one step that this one stands for
 };
 
 }  // namespace
@@ -255,7 +256,7 @@ struct adpsgd_ctx {
     RoundKeys rk{};
     bool timing = false;
     int32_t timing_every = 1;       // time every n-th launch of each class
-    int64_t class_count[kTimedClasses] = {};
+    int64_t class_seen[kTimedClasses] = {}, class_timed[kTimedClasses] = {};  // steps since timing was set
     std::deque<TimedLaunch> timed;
     int64_t timed_popped = 0;       // timed launches harvested so far (sequence of timed.front())
     std::vector<hipEvent_t> ev_pool;
@@ -328,7 +329,7 @@ int harvest(adpsgd_ctx *c, bool wait_all) {
         HIP_TRY(hipEventElapsedTime(&ms, tl.start, tl.stop));
         const int kind = tl.kind < 0 ? tStep : tl.kind;
         c->t_ms[kind] += ms;
-        c->t_n[kind] += 1;
+        c->t_n[kind] += tl.steps;
         c->ev_pool.push_back(tl.start);
         c->ev_pool.push_back(tl.stop);
         c->timed.pop_front();
@@ -337,18 +338,25 @@ int harvest(adpsgd_ctx *c, bool wait_all) {
     return ok();
 }
 
-// Launch, with HIP events around it when timing is on and this is the
-// sampled launch (every timing_every-th) of its class.  kind -1: decided later
-// (set_timed_kind).  *seq (may be null) receives the launch's sequence number,
-// or -1 when it is not timed.
+// Launch, with HIP events around it when timing is on and this launch is
+// sampled: a launch of `steps` steps counts as that many of its class, and is
+// timed when no more than one in timing_every of the class (rounded up) is
+// timed with it.  kind -1: decided later (set_timed_kind).  *seq (may be null)
+// receives the launch's sequence number, or -1 when it is not timed.
 template <class F>
-int timed_launch(adpsgd_ctx *c, int kind, F launch, int64_t *seq = nullptr) {
+int timed_launch(adpsgd_ctx *c, int kind, F launch, int64_t *seq = nullptr, int32_t steps = 1) {
     if (seq) *seq = -1;
     const int cls = kind < 0 ? cDeviceStep : kind;
-    if (!c->timing || (c->class_count[cls]++ % c->timing_every) != 0) {
+    bool sampled = false;
+    if (c->timing) {
+        c->class_seen[cls] += steps;
+        sampled = (c->class_timed[cls] + steps) * c->timing_every <= c->class_seen[cls] + c->timing_every - 1;
+    }
+    if (!sampled) {
         HIP_TRY(launch());
         return ok();
     }
+    c->class_timed[cls] += steps;
     if ((int)c->timed.size() >= kTimedMax) {
         int rc = harvest(c, false);
         if (rc) return rc;
@@ -357,7 +365,7 @@ int timed_launch(adpsgd_ctx *c, int kind, F launch, int64_t *seq = nullptr) {
             if (rc) return rc;
         }
     }
-    TimedLaunch tl{kind, nullptr, nullptr};
+    TimedLaunch tl{kind, nullptr, nullptr, steps};
     int rc = pool_event(c, &tl.start);
     if (rc) return rc;
     rc = pool_event(c, &tl.stop);
@@ -375,7 +383,7 @@ void set_timed_kind(adpsgd_ctx *c, int64_t seq, int kind) {
     if (seq >= 0 && i >= 0 && i < (int64_t)c->timed.size()) c->timed[(size_t)i].kind = kind;
 }
 
-StepParams step_params(const adpsgd_ctx *c, int64_t t) {
+StepParams step_params(const adpsgd_ctx *c, int64_t t, int32_t n = 1) {
     StepParams p;
     p.x = c->buf.x;
     p.m = c->buf.m;
@@ -389,18 +397,21 @@ StepParams step_params(const adpsgd_ctx *c, int64_t t) {
     p.sigma = (float)c->hp.sigma;
     p.mu = (float)c->hp.momentum;
     p.wd = (float)c->hp.weight_decay;
-    p.gamma = (float)adpsgd_lr(&c->hp, t);
+    p.n = n;
+    for (int32_t j = 0; j < n; ++j) p.gamma[j] = (float)adpsgd_lr(&c->hp, t + j);
     p.rk = c->rk;
     p.row_chunks = 1;  // set by launch_local_step from the launch shape
-    p.pad_ = 0;
     p.block0 = 0;
     return p;
 }
 
+// Steps t0 .. t0 + n - 1, up to kSpanSteps of them per launch.
 int enqueue_steps(adpsgd_ctx *c, int64_t t0, int64_t n) {
-    for (int64_t j = 0; j < n; ++j) {
-        const StepParams p = step_params(c, t0 + j);
-        int rc = timed_launch(c, tStep, [&] { return launch_local_step(p, c->vec, c->nontemporal, c->step_shape, c->stream); });
+    for (int64_t j = 0; j < n; j += kSpanSteps) {
+        const int32_t m = (int32_t)std::min<int64_t>(kSpanSteps, n - j);
+        const StepParams p = step_params(c, t0 + j, m);
+        int rc = timed_launch(
+            c, tStep, [&] { return launch_local_step(p, c->vec, c->nontemporal, c->step_shape, c->stream); }, nullptr, m);
         if (rc) return rc;
     }
     return ok();
@@ -501,7 +512,9 @@ int capture_run(adpsgd_ctx *c, int64_t t0, const std::vector<char> &due, int64_t
     for (size_t i = 0; i < due.size() && e == hipSuccess; ++i) {
         const int64_t t = t0 + (int64_t)i;
         if (!due[i]) {
-            e = launch_local_step(step_params(c, t), c->vec, c->nontemporal, c->step_shape, cs);
+            int32_t m = 1;
+            while (m < kSpanSteps && i + 1 < due.size() && !due[i + 1]) ++i, ++m;
+            e = launch_local_step(step_params(c, t, m), c->vec, c->nontemporal, c->step_shape, cs);
         } else {
             e = launch_tile_sync(sync_params(c, t), n_tiles, kFused, c->hp.avg_momentum != 0, c->vec, c->sync_nt, 0,
                                  cs);
@@ -970,12 +983,12 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
         return graph_mode ? c->h_gslots + (size_t)slot * c->slot_bytes : slot_host(c, slot);
     };
 
-    struct Entry { int64_t t; bool dev, uncertain; int slot; int64_t seq; };
+    struct Entry { int64_t t; bool dev, uncertain; int slot; int64_t seq; int32_t n; };   // n plain steps, or one of the device's
     std::deque<Entry> inflight;
     adpsgd_state known = c->st;   // the host controller after every accounted step
     Plan plan{true, known.cnt, known.p, known.p};
     bool dirty = false;
-    int64_t launched = t0, n_done = 0, n_slots = 0;
+    int64_t launched = t0, n_done = 0, n_slots = 0, n_launches = 0;
     int n_dev = 0, n_uncertain = 0;
     int status = ADPSGD_OK;
 
@@ -983,11 +996,11 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
     // host and check the device's record against the replay.
     auto account = [&](const Entry &e) -> int {
         int32_t due = 0;
-        (void)adpsgd_sched_step(&hp, &known, &due);
-        if (!e.dev) {
-            if (due) return fail(ADPSGD_ESTATE, "internal: a plain step ended a period");
-            return ADPSGD_OK;
+        for (int32_t j = 0; j < e.n; ++j) {
+            (void)adpsgd_sched_step(&hp, &known, &due);
+            if (!e.dev && due) return fail(ADPSGD_ESTATE, "internal: a plain step ended a period");
         }
+        if (!e.dev) return ADPSGD_OK;
         SlotHdr hdr;
         std::memcpy(&hdr, slot_rec(e.slot), sizeof hdr);
         const double *var = reinterpret_cast<const double *>(slot_rec(e.slot) + kSlotHdrBytes);
@@ -1072,7 +1085,7 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
         }
         int slot = 0;
         for (int64_t j = 0; j < n_steps; ++j) {
-            const Entry e{t0 + j, due[(size_t)j] != 0, false, due[(size_t)j] ? slot++ : -1, -1};
+            const Entry e{t0 + j, due[(size_t)j] != 0, false, due[(size_t)j] ? slot++ : -1, -1, 1};
             const int rc = account(e);
             if (rc && status == ADPSGD_OK) status = rc;
         }
@@ -1082,7 +1095,7 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
     }
     int hard = ADPSGD_OK;  // a HIP failure: stop at once
     while (hard == ADPSGD_OK) {
-        if ((launched - t0) % kPollEvery == 0) {
+        if (n_launches % kPollEvery == 0) {
             if ((hard = drain(false))) break;
             if (c->timing && (hard = harvest(c, false))) break;
         }
@@ -1093,7 +1106,8 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
         }
         if (dirty) {
             plan = Plan{true, known.cnt, known.p, known.p};
-            for (const Entry &e : inflight) (void)advance(plan, e.t);
+            for (const Entry &e : inflight)
+                for (int32_t j = 0; j < e.n; ++j) (void)advance(plan, e.t + j);
             dirty = false;
         }
         Plan next = plan;
@@ -1118,9 +1132,14 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
             hard = drain(true);
             continue;
         }
-        Entry e{launched, cls != cPlain, cls == cUncertain, -1, -1};
+        Entry e{launched, cls != cPlain, cls == cUncertain, -1, -1, 1};
         if (cls == cPlain) {
-            hard = enqueue_steps(c, launched, 1);
+            // with the plain steps that follow it, in one launch
+            for (Plan more = next; e.n < kSpanSteps && launched + e.n < end; ++e.n) {
+                if (advance(more, launched + e.n) != cPlain) break;
+                next = more;
+            }
+            hard = enqueue_steps(c, launched, e.n);
         } else {
             // a sync the host planned runs the fused kernel; the device's reduction
             // still confirms it and takes the decision
@@ -1134,7 +1153,8 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
         if (hard) break;
         inflight.push_back(e);
         plan = next;
-        ++launched;
+        launched += e.n;
+        ++n_launches;
     }
     // whatever was enqueued runs to completion and is accounted for
     hipError_t e = hipStreamSynchronize(c->stream);
@@ -1219,7 +1239,8 @@ extern "C" int adpsgd_set_timing(adpsgd_ctx *c, int32_t every) {
     c->timing = every != 0;
     c->timing_every = every > 0 ? every : 1;
     for (int i = 0; i < tKinds; ++i) { c->t_ms[i] = 0.0; c->t_n[i] = 0; }
-    for (auto &n : c->class_count) n = 0;
+    for (auto &n : c->class_seen) n = 0;
+    for (auto &n : c->class_timed) n = 0;
     c->graph_captures = c->graph_replays = 0;
     return ok();
 }
