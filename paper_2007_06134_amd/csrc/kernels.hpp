@@ -55,7 +55,8 @@ struct StepParams {
     int64_t n_groups;  // ceil(P / 4)
     int32_t K;
     uint32_t t;        // first step's index (Philox counter word 2)
-    float sigma, mu, wd;
+    float sigma_r;     // sigma sqrt(2 ln 2) (see add_noise2)
+    float mu, wd;
     int32_t n;         // steps of this launch: t .. t + n - 1 (k_local_step; the sync kernels take one)
     RoundKeys rk;
     // Chunks of one worker's row that an XCD takes one after another before
@@ -110,7 +111,7 @@ constexpr int kMaxRowChunks = 4096;
 // A launch of n >= kUncappedSteps steps leaves the LDS reservation out: it is
 // bound by arithmetic, not by HBM, and wants every wave it can hold (measured
 // with and without the 8 KB reservation, K = 8, P = 138M: 1 step 2.97 and 3.03
-// ms, 2 steps 3.02 and 3.05, 3 steps 3.16 and 3.10, 4 steps 3.52 and 3.26).
+// ms, 2 steps 3.01 and 3.05, 3 steps 3.18 and 3.10, 4 steps 3.55 and 3.27).
 constexpr int kUncappedSteps = 3;
 constexpr StepShape kStepShapes[] = {{64, 0, 1},     {64, 8192, 1},  {128, 0, 1},   {256, 0, 1},
                                      {64, 8192, 16}, {64, 8192, 32}, {64, 8192, 64}};

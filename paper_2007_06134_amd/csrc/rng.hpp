@@ -50,6 +50,48 @@ __device__ __forceinline__ u4 philox10(u4 c, const RoundKeys &rk) {
     return c;
 }
 
+// Three-input exclusive or (one v_bitop3_b32).
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
+// The noise words of group g: counter (g, k, t, 0).  With k and t uniform over
+// the wave, round 0's product of t is a scalar, and so is round 1's product of
+// the word it makes; the products of g in round 0 and of the word they make in
+// round 1 depend on g alone.  A lane that takes several workers or steps of
+// its group therefore forms those two once (philox_group), and every (k, t)
+// costs eight rounds of vector products instead of ten.
+struct PhiloxGroup {
+    uint32_t lo0;        // low word of g's product in round 0
+    uint32_t hi1, lo1;   // round 1's product of the word it makes
+};
+__device__ __forceinline__ PhiloxGroup philox_group(uint32_t g, const RoundKeys &rk) {
+    const uint64_t a = (uint64_t)g * 0xD2511F53u;
+    const uint32_t z = (uint32_t)(a >> 32) ^ rk.hi[0];
+    const uint64_t b = (uint64_t)z * 0xCD9E8D57u;
+    return PhiloxGroup{(uint32_t)a, (uint32_t)(b >> 32), (uint32_t)b};
+}
+__device__ __forceinline__ u4 philox_noise(const PhiloxGroup &pg, uint32_t k, uint32_t t, const RoundKeys &rk) {
+    const uint64_t pt = (uint64_t)t * 0xCD9E8D57u;                   // scalar: round 0
+    const uint32_t x = (uint32_t)(pt >> 32) ^ k ^ rk.lo[0];
+    const uint64_t px = (uint64_t)x * 0xD2511F53u;                   // scalar: round 1
+    u4 c;
+    c.x = pg.hi1 ^ ((uint32_t)pt ^ rk.lo[1]);
+    c.y = pg.lo1;
+    c.z = pg.lo0 ^ ((uint32_t)(px >> 32) ^ rk.hi[1]);
+    c.w = (uint32_t)px;
+#pragma unroll
+    for (int r = 2; r < 10; ++r) {
+        const uint64_t prod_a = (uint64_t)c.x * 0xD2511F53u;
+        const uint64_t prod_b = (uint64_t)c.z * 0xCD9E8D57u;
+        c.x = xor3((uint32_t)(prod_b >> 32), c.y, rk.lo[r]);
+        c.z = xor3((uint32_t)(prod_a >> 32), c.w, rk.hi[r]);
+        c.y = (uint32_t)prod_b;
+        c.w = (uint32_t)prod_a;
+    }
+    return c;
+}
+
 // Two Box-Muller normals from two words: radius sqrt(-2 ln u1) with
 // u1 = (hi24(a) + 1) 2^-24 in (0, 1] (never 0, so the log is finite) and angle
 // 2 pi u2 with u2 = hi24(b) 2^-24.  Both uniforms are exact in fp32.
@@ -72,6 +114,26 @@ __device__ __forceinline__ f4 normals4(u4 r) {
     box_muller2(r.x, r.y, z0, z1);
     box_muller2(r.z, r.w, z2, z3);
     return f4{z0, z1, z2, z3};
+}
+
+// base + sigma z for the two normals z of words a and b, with
+// s = sigma sqrt(2 ln 2): sigma times the radius is s sqrt(-log2 u1), so the
+// noise level and the logarithm's base cost one product for two normals, and
+// the cosine's and the sine's product takes the sum.  (hi24(a) + 1) 2^-24 is
+// exact in the fma.
+__device__ __forceinline__ void add_noise2(float s, uint32_t a, uint32_t b, float base0, float base1, float &d0,
+                                           float &d1) {
+    const float u1 = fmaf((float)(a >> 8), 0x1p-24f, 0x1p-24f);
+    const float u2 = (float)(b >> 8) * 0x1p-24f;
+    const float radius = s * __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1));
+    d0 = fmaf(radius, __builtin_amdgcn_cosf(u2), base0);
+    d1 = fmaf(radius, __builtin_amdgcn_sinf(u2), base1);
+}
+__device__ __forceinline__ f4 add_noise4(float s, u4 r, f4 base) {
+    float d0, d1, d2, d3;
+    add_noise2(s, r.x, r.y, base.x, base.y, d0, d1);
+    add_noise2(s, r.z, r.w, base.z, base.w, d2, d3);
+    return f4{d0, d1, d2, d3};
 }
 
 // Uniform in [0, 1) from the 24 high bits.

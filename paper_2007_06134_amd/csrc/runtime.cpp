@@ -394,7 +394,7 @@ StepParams step_params(const adpsgd_ctx *c, int64_t t, int32_t n = 1) {
     p.n_groups = (c->P + 3) / 4;
     p.K = c->K;
     p.t = (uint32_t)t;
-    p.sigma = (float)c->hp.sigma;
+    p.sigma_r = (float)(c->hp.sigma * std::sqrt(2.0 * M_LN2));
     p.mu = (float)c->hp.momentum;
     p.wd = (float)c->hp.weight_decay;
     p.n = n;
