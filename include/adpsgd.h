@@ -76,17 +76,18 @@ extern "C" {
                                     with t mod p == 0 (after steps 0, p, 2p, ...)           */
 
 /* ---- launch policies of adpsgd_run (adpsgd_set_launch_policy) ----------------- */
-#define ADPSGD_LAUNCH_HYBRID 0  /* default: steps the host can plan run as plain steps or
-                                   fused syncs; after a decisive sync the host waits for
-                                   its outcome while the GPU has queued work, else the
-                                   device decides the next steps itself.  A run in a
+#define ADPSGD_LAUNCH_HYBRID 0  /* default: a launch takes as many steps and syncs as the host
+                                   can plan (up to 64 steps and 16 syncs), up to and with
+                                   the first sync whose outcome may move the period; behind
+                                   such a sync the device ends launches itself, each with
+                                   its next sync, up to 3 ahead of the host.  A run in a
                                    constant-period mode on a problem of K * P < 2^24
                                    (launch-bound) and up to 65536 steps, with timing off,
                                    is captured once as a HIP graph of the same launches and
                                    replayed while runs repeat with the same start state,
                                    length and step launch shape                            */
-#define ADPSGD_LAUNCH_DEVICE 1  /* every step is decided on the device (step + optional
-                                   sync + reduction per step)                              */
+#define ADPSGD_LAUNCH_DEVICE 1  /* every step is a launch, decided on the device (step +
+                                   optional sync + reduction per step)                     */
 #define ADPSGD_LAUNCH_HOST 2    /* the host waits for every decision it needs; the device
                                    only confirms syncs the host planned                    */
 
@@ -131,9 +132,10 @@ typedef struct {
     float *h;               /* [P] curvatures, written by init                               */
     float *xstar;           /* [P] optimum, written by init                                  */
     void *workspace;        /* >= adpsgd_workspace_bytes(...) bytes, 256-byte aligned;
-                               tile, chunk and window tables, partial sums and the device
-                               copy of the controller state (the records of the reductions
-                               go to pinned host memory that the library allocates)          */
+                               tile, chunk and window tables, partial sums (of up to 16
+                               syncs, in up to 64 MB) and the device copy of the controller
+                               state (the records of the reductions go to pinned host
+                               memory that the library allocates)                            */
     size_t workspace_bytes;
     void *stream;           /* hipStream_t for every launch and copy; NULL = null stream     */
     int64_t row_stride;     /* elements from one row of x (and of m) to the next, >= P;
@@ -198,10 +200,11 @@ typedef struct {
 } adpsgd_step_rec;
 
 /* Per-kernel device time, from HIP events around the sampled launches.  A
- * launch of several steps counts as that many step launches. */
+ * launch of several steps counts as that many launches (a step that a sync
+ * follows as a fused one), its time shared evenly by its steps. */
 typedef struct {
     double step_ms;     int64_t step_launches;     /* plain local step            */
-    double fused_ms;    int64_t fused_launches;    /* last step of a period + sync */
+    double fused_ms;    int64_t fused_launches;    /* step + sync                 */
     double average_ms;  int64_t average_launches;  /* separate mean/broadcast/var */
     double segsum_ms;   int64_t segsum_launches;   /* reduction: per-tensor sums and,
                                                       in a run, the period decision */
@@ -280,10 +283,9 @@ ADPSGD_API int adpsgd_schedule(adpsgd_ctx *c, const double *var, int32_t *next_p
 ADPSGD_API int adpsgd_run(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_t log_cap,
                double *var_log, int64_t *n_syncs);
 
-/* adpsgd_run that also records every step in trace[0 .. trace_cap) (host):
- * plain steps run as a step that also reduces the variance and the gradient
- * norm at the mean without averaging (the same HBM traffic as a plain step),
- * sync steps as the fused step + sync that also reports the gradient norm.
+/* adpsgd_run that also records every step in trace[0 .. trace_cap) (host): every
+ * step of a launch is measured (the variance, and the gradient norm at the
+ * mean), whether a sync follows it or not, with the same HBM traffic.
  * The period-averaged variance V_t of Sec. III-A (eq. (vt)) follows from the
  * records: Var[W_k] is 0 at the first step of a period and trace[k-1].var at
  * the others. */

@@ -3,19 +3,19 @@
 //   k_local_step   1 to 64 local steps of every worker (Algorithm 2's update) in
 //                  one streaming pass over x and m, with the noisy quadratic
 //                  gradient generated in registers.
-//   k_sync_lds     the synchronization of Algorithm 2 on one aligned chunk
-//                  of 256 elements: replica mean, per-element squared deviations
-//                  (the parameter variance of Section II-B), broadcast of the
-//                  mean; optionally fused behind the period's last local step
-//                  so a sync costs no extra pass over HBM.
-//   k_sync_loop    the same for K above 64 and the separate sync at K = 3
-//                  (other K take k_sync_lds, compiled for powers of two up to
-//                  32 or with K as an argument).
+//   k_span         1 to 64 steps with the synchronizations among them (Algorithm
+//                  2: replica mean, broadcast, per-element squared deviations,
+//                  the parameter variance of Section II-B) on one aligned chunk
+//                  of 256 elements, in one pass over x and m (K up to 128).
+//   k_average      the synchronization alone (K up to 128 but 3).
+//   k_sync_loop    one step with a sync for K above 128; the sync alone there and
+//                  at K = 3.
 //   k_reduce_chunks,  fixed-order sums of the tile partials per chunk, then
 //   k_reduce_windows  per tensor (in windows of tensors when there are more
 //   k_reduce_finish   chunk partials than one block's LDS holds) and over
-//                     tensors, and Algorithm 2's period decision when a run's
-//                     schedule lives on the device.
+//   k_control         tensors, for every sync of a launch at once, and Algorithm
+//                     2's period decisions when a run's schedule lives on the
+//                     device.
 //   k_init_problem, k_zero_rows, k_philox_dump, k_normal_dump: problem data,
 //                  row clearing and the raw generator streams.
 //
@@ -35,6 +35,20 @@
 namespace adpsgd {
 
 namespace {
+
+// Bring the first BYTES of the kernel's arguments into the scalar cache in one
+// round trip, for a kernel of one block whose time is such round trips: read
+// batch after batch where they are used, they cost k_reduce_finish 4.2 us
+// instead of 3.5 (T = 1, 256 tiles).  The other kernels gain nothing by it.
+template <int BYTES>
+__device__ __forceinline__ void fetch_args() {
+    const auto *args = (const __attribute__((address_space(4))) uint32_t *)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t line[BYTES / 64 + 1];
+#pragma unroll
+    for (int i = 0; i <= BYTES / 64; ++i) line[i] = args[i < BYTES / 64 ? 16 * i : BYTES / 4 - 1];
+#pragma unroll
+    for (int i = 0; i <= BYTES / 64; ++i) asm volatile("" ::"s"(line[i]));
+}
 
 __device__ __forceinline__ f4 fma4(f4 a, f4 b, f4 c) {
     return f4{fmaf(a.x, b.x, c.x), fmaf(a.y, b.y, c.y), fmaf(a.z, b.z, c.z), fmaf(a.w, b.w, c.w)};
@@ -100,6 +114,14 @@ __device__ __forceinline__ void sgd_step(const StepParams &a, const GroupData &g
     x = fma4(splat(-a.gamma[j]), m, x);
 }
 
+// Sum of the squares of v's elements, in fp64.
+__device__ __forceinline__ double square_sum(f4 v) {
+    double q = (double)v.x * (double)v.x;
+    q = fma((double)v.y, (double)v.y, q);
+    q = fma((double)v.z, (double)v.z, q);
+    return fma((double)v.w, (double)v.w, q);
+}
+
 // Sums of a pair of values over the block in a fixed order: wave64 butterfly,
 // then the waves in order.  Valid on thread 0.  TWO = false: b is known to be
 // zero everywhere (no gradient norm outside tracing) and is not reduced.
@@ -132,16 +154,6 @@ __device__ __forceinline__ Pair block_sum2(double a, double b) {
         }
         return total;
     }
-}
-
-// Squared norm of the gradient of F(x) = 1/2 sum h (x - x*)^2 + wd/2 |x|^2 at
-// the replica mean, summed over the lanes of one group in [lo, hi).
-__device__ __forceinline__ double grad_norm2(const StepParams &a, f4 mean, f4 h, f4 xs, bool full, int64_t e0,
-                                             int64_t lo, int64_t hi) {
-    const f4 gr = fma4(h, mean - xs, splat(a.wd) * mean);
-    f4 g2 = gr * gr;
-    if (!full) g2 = mask4(g2, e0, lo, hi);
-    return ((double)g2.x + (double)g2.y) + ((double)g2.z + (double)g2.w);
 }
 
 // ---------------------------------------------------------------- local step
@@ -289,7 +301,7 @@ __device__ __forceinline__ f4 shfl_xor4(f4 v, int off) {
 // as tree_sum_lds<W>).  The means of the first n groups go to out[64]; callers
 // put a barrier before (the wave sums) and after (the means).  For a block of
 // 16 waves this reads 1/16 of the LDS that every wave reading all 16 sums
-// reads (+2 to +3% for the fused sync at K = 16 and 32; no gain at 8 waves).
+// reads (1-2% of the separate sync at K = 32).
 template <int W, int KT>
 __device__ __forceinline__ void group_means(const f4 (*sums)[64], f4 *out, int lane, int w, int n) {
     static_assert((W & (W - 1)) == 0 && (KT & (KT - 1)) == 0, "power-of-two waves and workers");
@@ -299,39 +311,6 @@ __device__ __forceinline__ void group_means(const f4 (*sums)[64], f4 *out, int l
 #pragma unroll
     for (int off = 1; off < W; off <<= 1) v = v + shfl_xor4(v, off);
     if (i == 0) out[j] = v * splat(1.0f / (float)KT);
-}
-
-// Step s.t of a run whose schedule lives on the device: does a sync follow
-// it?  Every thread reads the same state (written only by the reduction
-// kernel after a sync), so the answer is uniform over the launch.
-__device__ __forceinline__ bool device_due(const SyncParams &p) {
-    const SchedState s = *p.sched;
-    const int64_t t = (int64_t)p.s.t;
-    return sync_due(p.rule, s.cnt + (t - s.t) + 1, period_at(p.rule, s.p, t), t);
-}
-
-// One tile (at most 64 groups, one per lane) of one tensor.  Wave w owns the
-// rows k = R w .. R w + R - 1 (W waves, R = K / W rows each; see sync_waves).
-// Each thread steps its rows (modes with a step), publishes their pairwise sum
-// in LDS, reads the W sums of its lane back to form the mean in a fixed order
-// (the same bits in every thread, and the same as a tree over all K rows),
-// sums its squared deviations and, when a sync is due, writes the mean over
-// its rows (with averaged momentum, the momentum rows too).  The
-// traced mode also sums the squared gradient norm at the mean (wave 0 counts
-// each element once).  partials[2 tile + {0, 1}] = (sum of squared
-// deviations, gradient norm^2).  In kDevice a step without a sync stores the
-// stepped rows and measures nothing.  Lanes of groups cut by the tile bounds
-// use masked scalar accesses.
-// Waves per block: one per worker row (at most 16) when the rows are stepped;
-// the averaging-only mode does best with two rows per wave (measured +2 to +15%).
-// KT = 0: K is a kernel argument (a K up to 64 without a compiled variant,
-// with RD = 2 or 4 rows per wave, or K = 3 with one); see lds_mean for the
-// order of the mean.
-template <int KT, int MODE>
-constexpr int sync_waves() {
-    if constexpr (KT == 0) return 16;  // the most waves a block of the K-argument kernel has
-    else if constexpr (MODE == kAverage && KT >= 2) return KT / 2 < 16 ? KT / 2 : 16;
-    else return KT < 16 ? KT : 16;
 }
 
 // block_sum2 over a run-time number of waves (at most 16), in the same order.
@@ -357,17 +336,34 @@ __device__ __forceinline__ Pair block_sum2_waves(double a, double b, int waves) 
     return total;
 }
 
-// RAGGED (K an argument, K not a multiple of RD): the last wave holds fewer
-// rows; the missing ones count as zeros in its sum.
-template <int KT, bool VEC, bool NT, int MODE, bool AVGM, int RD = 0, bool RAGGED = false>
-__global__ void __launch_bounds__((64 * sync_waves<KT, MODE>())) k_sync_lds(SyncParams p) {
+// Waves per block of the separate sync: with no step to take, two rows per wave
+// beat one (+2 to +15%).  KT = 0: K is a kernel argument (a K up to 128 without
+// a compiled variant, with RD = 2, 4 or 8 rows per wave); 16 is the most waves
+// such a block has.
+template <int KT>
+constexpr int average_waves() {
+    if constexpr (KT == 0) return 16;
+    else if constexpr (KT >= 2) return KT / 2 < 16 ? KT / 2 : 16;
+    else return 1;
+}
+
+// The separate sync of one aligned chunk of 256 elements (at most 64 groups, one
+// per lane).  Wave w owns the rows k = R w .. R w + R - 1: it publishes their
+// pairwise sum in LDS, reads the W sums of its lane back to form the mean in a
+// fixed order (the same bits in every thread, and the same as a tree over all
+// K rows), sums its squared deviations and writes the mean over its rows (with
+// averaged momentum, the momentum rows too).  partials[2 tile] = the sum of
+// squared deviations of each tile of the chunk.  Lanes of groups cut by the
+// chunk's end use masked scalar accesses.  RAGGED (K an argument, K not a
+// multiple of RD): the last wave holds fewer rows; the missing ones count as
+// zeros in its sum.
+template <int KT, bool VEC, bool NT, bool AVGM, int RD = 0, bool RAGGED = false>
+__global__ void __launch_bounds__(64 * average_waves<KT>()) k_average(SyncParams p) {
     static_assert((KT == 0) == (RD > 0), "RD (rows per wave) is given exactly when K is an argument");
     static_assert(!RAGGED || RD >= 2, "a ragged last wave comes with several rows per wave");
-    constexpr int WMAX = sync_waves<KT, MODE>();
+    constexpr int WMAX = average_waves<KT>();
     constexpr int R = KT > 0 ? KT / WMAX : RD;
     const int W = KT > 0 ? WMAX : (p.s.K + (RD > 0 ? RD : 1) - 1) / (RD > 0 ? RD : 1);
-    constexpr bool STEP = MODE != kAverage;
-    constexpr bool GN = MODE == kDeviceTrace;
     // a block of 16 waves forms each group's mean once (group_means)
     constexpr bool SPLIT = KT > 0 && WMAX >= 16;
     // wave w owns rows R w .. R w + R - 1 and publishes their subtree sum
@@ -375,20 +371,14 @@ __global__ void __launch_bounds__((64 * sync_waves<KT, MODE>())) k_sync_lds(Sync
     __shared__ f4 mpart[AVGM ? WMAX : 1][64];
     __shared__ f4 means[SPLIT ? 64 : 1], mmeans[SPLIT && AVGM ? 64 : 1];
     const StepParams &a = p.s;
-    bool bcast = true;  // the host-decided modes always average
-    if constexpr (MODE == kDevice || MODE == kDeviceTrace) bcast = device_due(p);
-    const bool measure = MODE != kDevice || bcast;
-    const bool avg_m = AVGM && bcast;
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform, so k and its products are scalars
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     // the block's aligned chunk and its tiles (one per tensor in it)
     const int64_t c = p.s.block0 + blockIdx.x;
     const int64_t lo = c * kTileElems, hi = lo + kTileElems < a.P ? lo + kTileElems : a.P;
     // The chunk's first tile and the next chunk's.  Blocks of 16 waves read
     // them as scalars here; smaller blocks load them in lanes 0 and 1 (a
     // vector load, so that no wait for them comes ahead of the row loads) and
-    // take them after the barrier.  Measured on the fused step + sync: the
-    // vector load 2% faster at K = 8, the scalars 0.3-2% faster at K >= 16.
+    // take them after the barrier.
     constexpr bool SEG_VEC = WMAX < 16;
     int32_t s0 = 0, s1 = 0, seg_l = 0;
     if constexpr (SEG_VEC) {
@@ -397,16 +387,14 @@ __global__ void __launch_bounds__((64 * sync_waves<KT, MODE>())) k_sync_lds(Sync
         s0 = p.chunk_seg[c];
         s1 = p.chunk_seg[c + 1];
     }
-    const int64_t g = (lo >> 2) + lane;
-    const int64_t e0 = 4 * g;
+    const int64_t e0 = 4 * ((lo >> 2) + lane);
     const bool active = e0 < hi;
     const bool full = VEC && e0 + 4 <= hi;
-    // row R w + r exists (only the last wave's second row can be missing)
+    // row R w + r exists (only the last wave's last rows can be missing)
     bool has[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) has[r] = !RAGGED || R * w + r < a.K;
     f4 xr[R];
-    f4 h = splat(0.0f), xs = splat(0.0f);
     if (active) {
         f4 m[R];
 #pragma unroll
@@ -414,40 +402,16 @@ __global__ void __launch_bounds__((64 * sync_waves<KT, MODE>())) k_sync_lds(Sync
             xr[r] = splat(0.0f);
             m[r] = splat(0.0f);
             if (!has[r]) continue;
-            float *xrow = a.x + (int64_t)(R * w + r) * a.ld + e0;
+            const float *xrow = a.x + (int64_t)(R * w + r) * a.ld + e0;
             xr[r] = full ? ld4<NT>(xrow) : ld4_masked(xrow, e0, lo, hi);
-            if (STEP || AVGM) {
-                float *mrow = a.m + (int64_t)(R * w + r) * a.ld + e0;
+            if (AVGM) {
+                const float *mrow = a.m + (int64_t)(R * w + r) * a.ld + e0;
                 m[r] = full ? ld4<NT>(mrow) : ld4_masked(mrow, e0, lo, hi);
             }
         }
-        if (STEP || GN) {
-            if (full) { h = ld4<false>(a.h + e0); xs = ld4<false>(a.xs + e0); }
-            else { h = ld4_masked(a.h + e0, e0, lo, hi); xs = ld4_masked(a.xs + e0, e0, lo, hi); }
-        }
-        if (STEP) {
-            const GroupData gd = group_data(a, g, h, xs);
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                if (!has[r]) continue;
-                const int k = R * w + r;
-                sgd_step(a, gd, k, xr[r], m[r]);
-                if (!avg_m) {
-                    float *mrow = a.m + (int64_t)k * a.ld + e0;
-                    if (full) st4<NT>(mrow, m[r]); else st4_masked(mrow, m[r], e0, lo, hi);
-                }
-                if (!bcast) {     // no sync: the replicas keep their new values
-                    float *xrow = a.x + (int64_t)k * a.ld + e0;
-                    if (full) st4<NT>(xrow, xr[r]); else st4_masked(xrow, xr[r], e0, lo, hi);
-                }
-            }
-        }
-        if (measure) {  // (rows a ragged last wave lacks hold zeros)
-            part[w][lane] = tree_sum_regs<R>(xr, 0);
-            if (AVGM) mpart[w][lane] = tree_sum_regs<R>(m, 0);
-        }
+        part[w][lane] = tree_sum_regs<R>(xr, 0);   // (rows a ragged last wave lacks hold zeros)
+        if (AVGM) mpart[w][lane] = tree_sum_regs<R>(m, 0);
     }
-    if (!measure) return;  // uniform over the block
     __syncthreads();
     if constexpr (SEG_VEC) {
         s0 = __builtin_amdgcn_readlane(seg_l, 0);
@@ -455,8 +419,8 @@ __global__ void __launch_bounds__((64 * sync_waves<KT, MODE>())) k_sync_lds(Sync
     }
     const bool one_tile = s1 - s0 == 1;   // uniform over the block
     if constexpr (SPLIT) {
-        // groups of the tile with elements in [lo, hi): the lanes that stored a sum
-        const int64_t n64 = (hi - 4 * (lo >> 2) + 3) / 4;
+        // groups of the chunk with elements in [lo, hi): the lanes that stored a sum
+        const int64_t n64 = (hi - lo + 3) / 4;
         const int n = n64 < 64 ? (int)n64 : 64;
         group_means<WMAX, KT>(part, means, lane, w, n);
         if (AVGM) group_means<WMAX, KT>(mpart, mmeans, lane, w, n);
@@ -464,8 +428,8 @@ __global__ void __launch_bounds__((64 * sync_waves<KT, MODE>())) k_sync_lds(Sync
     }
     // a chunk of one tile sums its squared deviations per row; a chunk of
     // several keeps them per element (over the rows), to split them by tile
-    double acc = 0.0, gn = 0.0;
-    double acc4[4] = {0.0, 0.0, 0.0, 0.0}, gn4[4] = {0.0, 0.0, 0.0, 0.0};
+    double acc = 0.0;
+    double acc4[4] = {0.0, 0.0, 0.0, 0.0};
     if (active) {
         f4 mean;
         if constexpr (SPLIT) mean = means[lane];
@@ -473,24 +437,20 @@ __global__ void __launch_bounds__((64 * sync_waves<KT, MODE>())) k_sync_lds(Sync
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if (!has[r]) continue;
-            // squared deviations in fp32 per element, each row's sum in fp64
-            const f4 dk = mean - xr[r];
-            f4 d2 = dk * dk;
-            if (!full) d2 = mask4(d2, e0, lo, hi);
+            f4 d = mean - xr[r];
+            if (!full) d = mask4(d, e0, lo, hi);
             if (one_tile) {
-                acc += ((double)d2.x + (double)d2.y) + ((double)d2.z + (double)d2.w);
+                acc += square_sum(d);
             } else {
-                acc4[0] += (double)d2.x;
-                acc4[1] += (double)d2.y;
-                acc4[2] += (double)d2.z;
-                acc4[3] += (double)d2.w;
+                acc4[0] = fma((double)d.x, (double)d.x, acc4[0]);
+                acc4[1] = fma((double)d.y, (double)d.y, acc4[1]);
+                acc4[2] = fma((double)d.z, (double)d.z, acc4[2]);
+                acc4[3] = fma((double)d.w, (double)d.w, acc4[3]);
             }
-            if (bcast) {
-                float *xrow = a.x + (int64_t)(R * w + r) * a.ld + e0;
-                if (full) st4<NT>(xrow, mean); else st4_masked(xrow, mean, e0, lo, hi);
-            }
+            float *xrow = a.x + (int64_t)(R * w + r) * a.ld + e0;
+            if (full) st4<NT>(xrow, mean); else st4_masked(xrow, mean, e0, lo, hi);
         }
-        if (avg_m) {
+        if (AVGM) {
             f4 mmean;
             if constexpr (SPLIT) mmean = mmeans[lane];
             else mmean = lds_mean<KT, WMAX, RD>(mpart, lane, W, a.K);
@@ -501,27 +461,14 @@ __global__ void __launch_bounds__((64 * sync_waves<KT, MODE>())) k_sync_lds(Sync
                 if (full) st4<NT>(mrow, mmean); else st4_masked(mrow, mmean, e0, lo, hi);
             }
         }
-        if (GN && w == 0) {
-            if (one_tile) {
-                gn = grad_norm2(a, mean, h, xs, full, e0, lo, hi);
-            } else {
-                const f4 gr = fma4(h, mean - xs, splat(a.wd) * mean);
-                f4 g2 = gr * gr;
-                if (!full) g2 = mask4(g2, e0, lo, hi);
-                gn4[0] = g2.x;
-                gn4[1] = g2.y;
-                gn4[2] = g2.z;
-                gn4[3] = g2.w;
-            }
-        }
     }
     if (one_tile) {
         Pair total;
-        if constexpr (KT > 0) total = block_sum2<WMAX, GN>(acc, gn);
-        else total = block_sum2_waves<GN>(acc, gn, W);
+        if constexpr (KT > 0) total = block_sum2<WMAX, false>(acc, 0.0);
+        else total = block_sum2_waves<false>(acc, 0.0, W);
         if (threadIdx.x == 0) {
             p.partials[2 * s0] = total.a;
-            p.partials[2 * s0 + 1] = total.b;
+            p.partials[2 * s0 + 1] = 0.0;
         }
         return;
     }
@@ -529,39 +476,305 @@ __global__ void __launch_bounds__((64 * sync_waves<KT, MODE>())) k_sync_lds(Sync
     // the elements in its range
     for (int32_t sgi = s0; sgi < s1; ++sgi) {
         const Tile t = p.tiles[sgi];
-        double v = 0.0, gv = 0.0;
+        double v = 0.0;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            if (in(e0 + j, t.start, t.start + t.len)) {
-                v += acc4[j];
-                gv += gn4[j];
-            }
+            if (in(e0 + j, t.start, t.start + t.len)) v += acc4[j];
         Pair total;
-        if constexpr (KT > 0) total = block_sum2<WMAX, GN>(v, gv);
-        else total = block_sum2_waves<GN>(v, gv, W);
+        if constexpr (KT > 0) total = block_sum2<WMAX, false>(v, 0.0);
+        else total = block_sum2_waves<false>(v, 0.0, W);
         if (threadIdx.x == 0) {
             p.partials[2 * sgi] = total.a;
-            p.partials[2 * sgi + 1] = total.b;
+            p.partials[2 * sgi + 1] = 0.0;
         }
         __syncthreads();   // the block sum's LDS is used again for the next tile
     }
 }
 
-// Any K: one wave per tile, lane = group, the workers walked in a loop.  The
-// first pass steps and stores the replicas (modes with a step) and sums them;
-// the second re-reads them for the deviations and, when a sync is due, writes
-// the mean.  With averaged momentum the first pass also sums the momentum
-// buffers and the second writes their mean.  In kDevice a step without a sync
-// is the first pass alone.
-template <bool VEC, int MODE, bool AVGM>
-__global__ void __launch_bounds__(64) k_sync_loop(SyncParams p) {
-    constexpr bool STEP = MODE != kAverage;
-    constexpr bool GN = MODE == kDeviceTrace;
+// ---------------------------------------------------------------- spans
+
+// Sum over the wave, in every lane: lanes i and i ^ 1, then i ^ 2, quads and
+// rows of 16 by mirroring (the same pairs of sums as i ^ 4 and i ^ 8), then the
+// row and half swaps.  All 64 lanes take part.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    v = dpp_add<0xB1>(v);    // quad_perm [1, 0, 3, 2]
+    v = dpp_add<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+    v = dpp_add<0x141>(v);   // row_half_mirror
+    v = dpp_add<0x140>(v);   // row_mirror
+    {
+        const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+        v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+    }
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+// Access to the first `left` elements of a group (at most 4; none when left <= 0).
+__device__ __forceinline__ f4 ld4_left(const float *base, int left) {
+    f4 v = splat(0.0f);
+    if (left > 0) v.x = base[0];
+    if (left > 1) v.y = base[1];
+    if (left > 2) v.z = base[2];
+    if (left > 3) v.w = base[3];
+    return v;
+}
+__device__ __forceinline__ void st4_left(float *base, f4 v, int left) {
+    if (left > 0) base[0] = v.x;
+    if (left > 1) base[1] = v.y;
+    if (left > 2) base[2] = v.z;
+    if (left > 3) base[3] = v.w;
+}
+// v's elements first + i that lie in [begin, begin + len), the others zero.
+__device__ __forceinline__ f4 mask4_range(f4 v, int first, int begin, int len) {
+    const uint32_t i = (uint32_t)(first - begin), n = (uint32_t)len;
+    return f4{i < n ? v.x : 0.0f, i + 1 < n ? v.y : 0.0f, i + 2 < n ? v.z : 0.0f, i + 3 < n ? v.w : 0.0f};
+}
+
+template <int N>
+__device__ __forceinline__ double tree_sum_regs_d(const double *v, int base) {
+    if constexpr (N == 1) return v[base];
+    else return tree_sum_regs_d<N / 2>(v, base) + tree_sum_regs_d<N - N / 2>(v, base + N / 2);
+}
+template <int N>
+__device__ __forceinline__ double tree_sum_lds_d(const double (*rows)[64], int lane, int base) {
+    if constexpr (N == 1) {
+        return rows[base][lane];
+    } else {
+        const double l = tree_sum_lds_d<N / 2>(rows, lane, base);
+        const double r = tree_sum_lds_d<N - N / 2>(rows, lane, base + N / 2);
+        return l + r;
+    }
+}
+
+// Waves per block of k_span with R rows per wave (K an argument: at most 16).
+template <int KT, int R>
+constexpr int span_waves() {
+    if constexpr (KT == 0) return 16;
+    else return KT / R;
+}
+
+// Waves per SIMD that k_span's registers leave room for, at least.
+template <int KT, int R>
+constexpr int span_occupancy() {
+    if constexpr (R == 1) return 8;
+    else if constexpr (R == 2) return KT > 0 ? (KT / R > 8 ? 8 : 7) : 6;
+    else if constexpr (KT > 0 && R == 4) return 5;
+    else return 4;
+}
+
+// Several steps and the syncs among them on one aligned chunk of 256 elements
+// (at most 64 groups, one per lane): a step couples no two elements and a sync
+// only the K replicas of one, so x and m stay in registers for the whole span
+// and cross HBM once.  Wave w owns the rows k = R w .. R w + R - 1.  After a
+// step that a sync follows (or after every step when all are measured), the
+// waves exchange their rows' pairwise sums through LDS, every thread forms the
+// mean in a fixed order (see lds_mean), and the squared deviations are added
+// over the rows pairwise and then over the lanes, by one wave of the block
+// (each measurement another one, so that the extra work spreads over the
+// SIMDs).  For a compiled K (a power of two) both sums are trees of which a
+// wave's rows are a node, so every R gives the same bits.  The measurement of
+// the span's j-th measured step goes to partials[j slot_stride + 2 tile + {0, 1}] =
+// (sum of squared deviations, squared gradient norm at the mean; the latter
+// only when every step is measured).
+//
+// Which steps a sync follows is planned by the host (when.syncs), or the span
+// ends with the first step that Algorithm 2's counter, read from the device's
+// controller state, says is due (when.device; span_plan).
+//
+// Bound: a span of one step by HBM, of five and more by vector arithmetic, about
+// 290 cycles a wave and step.  At K = 8, P = 138M with the sync at the end, 1 / 2
+// / 4 / 8 steps take 3.09 / 3.13 / 3.24 / 5.0 ms (the steps one by one, then the
+// step with its sync: 3.05 / 6.0 / 11.9 / 23.7 ms); 64 steps with a sync every
+// eighth 32.8 ms, 0.51 ms a step.
+template <int KT, int R, bool VEC, bool NT>
+__global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT, R>())) k_span(SpanParams p) {
+    constexpr int WMAX = span_waves<KT, R>();
     const StepParams &a = p.s;
-    bool bcast = true;
-    if constexpr (MODE == kDevice || MODE == kDeviceTrace) bcast = device_due(p);
-    const bool measure = MODE != kDevice || bcast;
-    const bool avg_m = AVGM && bcast;
+    const int K = KT > 0 ? KT : a.K;
+    const int W = KT > 0 ? WMAX : (K + R - 1) / R;
+    // blocks of 8 and 16 waves form each group's mean once (group_means)
+    constexpr bool SPLIT = KT > 0 && WMAX >= 8;
+    __shared__ f4 part[WMAX][64];
+    __shared__ f4 means[SPLIT ? 64 : 1];
+    __shared__ double dev[WMAX][64];
+    const SpanPlan sp = span_plan(p.when, p.sched, p.rule);
+    if (sp.n == 0) return;
+    const int lane = threadIdx.x & 63;
+    const int w = WMAX > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    const int64_t c = a.block0 + blockIdx.x;
+    const int64_t lo = c * kTileElems, hi = lo + kTileElems < a.P ? lo + kTileElems : a.P;
+    const int64_t g = (lo >> 2) + lane;
+    const int e = 4 * lane;                // the lane's first element in the chunk
+    const int len = (int)(hi - lo), left = len - e;
+    // the whole chunk moves as float4 groups (uniform), or single lanes are cut or unaligned
+    const bool whole = VEC && len == (int)kTileElems;
+    const bool full = VEC && left >= 4;
+    bool has[R];   // row R w + r exists (uniform; only the last wave's last rows can be missing)
+#pragma unroll
+    for (int r = 0; r < R; ++r) has[r] = KT > 0 || R == 1 || R * w + r < K;
+    // uniform row addresses (the lane's offset is 32 bits)
+    float *const xb = a.x + (int64_t)(R * w) * a.ld + lo;
+    float *const mb = a.m + (int64_t)(R * w) * a.ld + lo;
+    f4 x[R], m[R], h, xs;
+    if (whole) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            x[r] = m[r] = splat(0.0f);
+            if (!has[r]) continue;
+            x[r] = ld4<NT>(xb + r * a.ld + e);
+            m[r] = ld4<NT>(mb + r * a.ld + e);
+        }
+        h = ld4<false>(a.h + lo + e);
+        xs = ld4<false>(a.xs + lo + e);
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            x[r] = m[r] = splat(0.0f);
+            if (!has[r]) continue;
+            x[r] = full ? ld4<NT>(xb + r * a.ld + e) : ld4_left(xb + r * a.ld + e, left);
+            m[r] = full ? ld4<NT>(mb + r * a.ld + e) : ld4_left(mb + r * a.ld + e, left);
+        }
+        // (h and x* are aligned whatever the rows' stride)
+        h = left >= 4 ? ld4<false>(a.h + lo + e) : ld4_left(a.h + lo + e, left);
+        xs = left >= 4 ? ld4<false>(a.xs + lo + e) : ld4_left(a.xs + lo + e, left);
+    }
+    // the chunk's first tile and the next chunk's, in lanes 0 and 1: a vector
+    // load, so that no wait for it comes ahead of the row loads
+    const int32_t seg_l = p.chunk_seg[c + (lane & 1)];
+    const GroupData gd = group_data(a, g, h, xs);
+    const int j0 = (int)(sp.t - p.when.t);   // the first step's rate is gamma[j0]
+    int slot = 0;
+#pragma unroll 1
+    for (int j = 0; j < sp.n; ++j) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (has[r]) sgd_step(a, gd, R * w + r, x[r], m[r], j0 + j);
+        const bool due = (sp.syncs >> j) & 1;
+        if (!due && !p.when.measure) continue;   // uniform over the block
+
+        // the mean of the K rows v at every lane (part and means are free on entry)
+        auto row_mean = [&](const f4 *v) -> f4 {
+            if constexpr (WMAX == 1) return tree_sum_regs<R>(v, 0) * splat(1.0f / (float)KT);
+            part[w][lane] = tree_sum_regs<R>(v, 0);   // (rows a ragged last wave lacks hold zeros)
+            __syncthreads();
+            if constexpr (SPLIT) {
+                group_means<WMAX, KT>(part, means, lane, w, 64);
+                __syncthreads();
+                return means[lane];
+            }
+            return lds_mean<KT, WMAX, R>(part, lane, W, K);
+        };
+        const f4 mean = row_mean(x);
+        if (due && p.avg_m) {
+            if constexpr (WMAX > 1) __syncthreads();   // part and means are read
+            const f4 mmean = row_mean(m);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (has[r]) m[r] = mmean;
+        }
+        const int32_t s0 = __builtin_amdgcn_readlane(seg_l, 0), s1 = __builtin_amdgcn_readlane(seg_l, 1);
+        const bool summer = WMAX == 1 || w == (int)((uint32_t)(c + slot) % (uint32_t)W);
+        double *const out = p.partials + (int64_t)slot * p.slot_stride;
+        // one sum per tile (tensor) of the chunk; usually all of the chunk is one
+        for (int32_t sgi = s0; sgi < s1; ++sgi) {
+            int begin = 0, n = len;
+            if (s1 - s0 > 1) {
+                const Tile t = p.tiles[sgi];
+                begin = (int)(t.start - lo);
+                n = t.len;
+            }
+            const bool cut = n < (int)kTileElems;   // uniform
+            double q[KT > 0 ? R : 1];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                f4 d = mean - x[r];
+                if (cut) d = mask4_range(d, e, begin, n);
+                if constexpr (KT > 0) q[r] = square_sum(d);
+                else if (r == 0) q[0] = square_sum(d);   // (every wave has a first row)
+                else if (has[r]) q[0] += square_sum(d);
+            }
+            double v;
+            if constexpr (KT > 0) v = tree_sum_regs_d<R>(q, 0);
+            else v = q[0];
+            if constexpr (WMAX > 1) {
+                dev[w][lane] = v;
+                __syncthreads();
+                if (summer) {
+                    if constexpr (KT > 0) {
+                        v = tree_sum_lds_d<WMAX>(dev, lane, 0);
+                    } else {
+                        v = dev[0][lane];
+                        for (int i = 1; i < W; ++i) v += dev[i][lane];
+                    }
+                }
+                if (s1 - s0 > 1) __syncthreads();   // dev is read before the next tile's sums
+            }
+            if (summer) {
+                v = wave_sum(v);
+                double gn = 0.0;
+                if (p.when.measure) {
+                    f4 gr = fma4(gd.hw, mean - gd.xs, gd.wxs);   // h (mean - x*) + wd mean
+                    if (cut) gr = mask4_range(gr, e, begin, n);
+                    gn = wave_sum(square_sum(gr));
+                }
+                if (lane == 0) {
+                    out[2 * (int64_t)sgi] = v;
+                    out[2 * (int64_t)sgi + 1] = gn;
+                }
+            }
+        }
+        if (due) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (has[r]) x[r] = mean;
+        }
+        ++slot;
+    }
+    if (whole) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (!has[r]) continue;
+            st4<NT>(xb + r * a.ld + e, x[r]);
+            st4<NT>(mb + r * a.ld + e, m[r]);
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (!has[r]) continue;
+            if (full) st4<NT>(xb + r * a.ld + e, x[r]); else st4_left(xb + r * a.ld + e, x[r], left);
+            if (full) st4<NT>(mb + r * a.ld + e, m[r]); else st4_left(mb + r * a.ld + e, m[r], left);
+        }
+    }
+}
+
+// K above 128 (and the separate sync at K = 3): one wave per tile, lane = group,
+// the workers walked in a loop.  The first pass takes the span's one step (with
+// STEP), stores the replicas and sums them; the second re-reads them for the
+// deviations and, when a sync is due, writes the mean.  With averaged momentum
+// the first pass also sums the momentum buffers and the second writes their
+// mean.  A step that is neither synced nor measured is the first pass alone.
+template <bool VEC, bool STEP>
+__global__ void __launch_bounds__(64) k_sync_loop(SpanParams p) {
+    const StepParams &a = p.s;
+    bool bcast = true, measure = true;
+    int j = 0;
+    if constexpr (STEP) {
+        const SpanPlan sp = span_plan(p.when, p.sched, p.rule);
+        if (sp.n == 0) return;
+        j = (int)(sp.t - p.when.t);
+        bcast = sp.syncs & 1;
+        measure = bcast || p.when.measure;
+    }
+    const bool grad = STEP && p.when.measure;
+    const bool sum_m = p.avg_m, avg_m = sum_m && bcast;
     const int64_t ti = p.s.block0 + blockIdx.x;
     const Tile tile = p.tiles[ti];
     const int64_t lo = tile.start, hi = tile.start + tile.len;
@@ -571,7 +784,7 @@ __global__ void __launch_bounds__(64) k_sync_loop(SyncParams p) {
     if (e0 < hi) {
         const bool full = VEC && e0 >= lo && e0 + 4 <= hi;
         f4 h = splat(0.0f), xs = splat(0.0f);
-        if (STEP || GN) {
+        if (STEP) {
             if (full) { h = ld4<false>(a.h + e0); xs = ld4<false>(a.xs + e0); }
             else { h = ld4_masked(a.h + e0, e0, lo, hi); xs = ld4_masked(a.xs + e0, e0, lo, hi); }
         }
@@ -582,14 +795,14 @@ __global__ void __launch_bounds__(64) k_sync_loop(SyncParams p) {
             float *mrow = a.m + (int64_t)k * a.ld + e0;
             f4 x = full ? ld4<false>(xrow) : ld4_masked(xrow, e0, lo, hi);
             f4 m = splat(0.0f);
-            if (STEP || AVGM) m = full ? ld4<false>(mrow) : ld4_masked(mrow, e0, lo, hi);
+            if (STEP || sum_m) m = full ? ld4<false>(mrow) : ld4_masked(mrow, e0, lo, hi);
             if (STEP) {
-                sgd_step(a, gd, k, x, m);
+                sgd_step(a, gd, k, x, m, j);
                 if (full) st4<false>(xrow, x); else st4_masked(xrow, x, e0, lo, hi);
                 if (!avg_m) { if (full) st4<false>(mrow, m); else st4_masked(mrow, m, e0, lo, hi); }
             }
             s = (k == 0) ? x : s + x;
-            if (AVGM) sm = (k == 0) ? m : sm + m;
+            if (sum_m) sm = (k == 0) ? m : sm + m;
         }
         if (measure) {
             const f4 mean = s / splat((float)a.K);
@@ -597,22 +810,24 @@ __global__ void __launch_bounds__(64) k_sync_loop(SyncParams p) {
             for (int k = 0; k < a.K; ++k) {
                 float *xrow = a.x + (int64_t)k * a.ld + e0;
                 const f4 x = full ? ld4<false>(xrow) : ld4_masked(xrow, e0, lo, hi);
-                // squared deviations in fp32 per element, each row's sum in fp64
-                const f4 dk = mean - x;
-                f4 d2 = dk * dk;
-                if (!full) d2 = mask4(d2, e0, lo, hi);
-                acc += ((double)d2.x + (double)d2.y) + ((double)d2.z + (double)d2.w);
+                f4 d = mean - x;
+                if (!full) d = mask4(d, e0, lo, hi);
+                acc += square_sum(d);
                 if (bcast) { if (full) st4<false>(xrow, mean); else st4_masked(xrow, mean, e0, lo, hi); }
                 if (avg_m) {
                     float *mrow = a.m + (int64_t)k * a.ld + e0;
                     if (full) st4<false>(mrow, mmean); else st4_masked(mrow, mmean, e0, lo, hi);
                 }
             }
-            if (GN) gn = grad_norm2(a, mean, h, xs, full, e0, lo, hi);
+            if (grad) {
+                f4 gr = fma4(gd.hw, mean - gd.xs, gd.wxs);
+                if (!full) gr = mask4(gr, e0, lo, hi);
+                gn = square_sum(gr);
+            }
         }
     }
     if (!measure) return;
-    const Pair total = block_sum2<1, GN>(acc, gn);
+    const Pair total = block_sum2<1>(acc, gn);
     if (threadIdx.x == 0) {
         p.partials[2 * ti] = total.a;
         p.partials[2 * ti + 1] = total.b;
@@ -621,52 +836,88 @@ __global__ void __launch_bounds__(64) k_sync_loop(SyncParams p) {
 
 // ---------------------------------------------------------------- reduction
 
-__device__ __forceinline__ void write_hdr(const ReduceParams &r, int32_t due, int32_t p, int32_t p_next,
-                                          int32_t status, double S, double GN, const SchedState &st) {
+// The step that the launch's slot-th measurement followed, and whether a sync
+// did too: every step in turn when all are measured, else the syncs' steps.
+// False if the launch has no such measurement.
+__device__ __forceinline__ bool slot_step(const ReduceParams &r, const SpanPlan &sp, int slot, int *j, bool *due) {
+    if (r.when.measure) {
+        *j = slot;
+        *due = slot < sp.n && ((sp.syncs >> slot) & 1);
+        return slot < sp.n;
+    }
+    uint64_t left = sp.syncs;
+    for (int i = 0; i < slot; ++i) left &= left - 1;
+    *due = left != 0;
+    *j = left ? __ffsll((unsigned long long)left) - 1 : 0;
+    return left != 0;
+}
+
+__device__ __forceinline__ SlotHdr *slot_hdr(const ReduceParams &r, int slot) {
+    int i = r.slot0 + slot;   // (a launch has no more slots than the ring)
+    if (i >= r.ring) i -= r.ring;
+    return reinterpret_cast<SlotHdr *>(r.recs + (int64_t)i * r.slot_bytes);
+}
+
+__device__ __forceinline__ void write_hdr(SlotHdr *to, int64_t t, int32_t n, bool due, int32_t p, int32_t p_next,
+                                          int32_t status, double S, double GN, double C2, int64_t nC2) {
     SlotHdr h;
-    h.t = r.t;
-    h.due = due;
+    h.t = t;
+    h.due = due ? 1 : 0;
     h.p = p;
     h.p_next = p_next;
     h.status = status;
     h.S = S;
     h.GN = GN;
-    h.C2 = st.C2;
-    h.nC2 = st.nC2;
-    *r.hdr = h;
+    h.C2 = C2;
+    h.nC2 = nC2;
+    h.n = n;
+    h.pad_ = 0;
+    *to = h;
 }
 
-// Is there a sync (or, when tracing, a step) to reduce?  Without a schedule
-// the caller decided there is one.  Uniform over a launch: the state changes
-// only at the end of k_reduce_finish.
-__device__ __forceinline__ bool reduce_due(const ReduceParams &r, int32_t *p_t, SchedState *st) {
-    *p_t = 0;
-    *st = SchedState{};
-    if (!r.sched) return true;
-    *st = *r.sched;
-    *p_t = period_at(r.rule, st->p, r.t);
-    return sync_due(r.rule, st->cnt + (r.t - st->t) + 1, *p_t, r.t);
+// Algorithm 2's sampling and period decision for one measurement (the same
+// apply_sync as the host controller), and its record.
+__device__ __forceinline__ void control_slot(const ReduceParams &r, const SpanPlan &sp, int slot, int j, bool due,
+                                             double S, double GN, SchedState *st) {
+    const int64_t t = sp.t + j;
+    const int32_t p_t = period_at(r.rule, st->p, t);
+    int32_t status = ADPSGD_OK;
+    if (due) {
+        st->p = p_t;
+        // a non-finite S restarts the counter and moves nothing else
+        if (!apply_sync(r.rule, t, r.gamma[t - r.when.t], S, st, nullptr)) status = ADPSGD_ENONFINITE;
+    }
+    write_hdr(slot_hdr(r, slot), t, sp.n, due, p_t, due ? st->p : p_t, status, S, GN, st->C2, st->nC2);
 }
 
-// Level 1, one wave per chunk (kChunksPerBlock chunks per block): the chunk's
-// tile partials, summed in a fixed order (strided over the lanes, then a
-// butterfly).  A chunk holds at most kChunkTiles = 1024 tiles, 16 per lane;
-// problems of thousands of small tensors have as many one-tile chunks, which
-// would otherwise cost a block each.
+// The controller state after the span: t, and the steps since its last sync.
+__device__ __forceinline__ void end_span(const ReduceParams &r, const SpanPlan &sp, SchedState *st) {
+    const int64_t since = sp.syncs ? sp.n - (64 - __clzll((long long)sp.syncs)) : st->cnt + (sp.t - st->t) + sp.n;
+    st->cnt = since;
+    st->t = sp.t + sp.n;
+}
+
+// Level 1, one wave per chunk (kChunksPerBlock chunks per block), blockIdx.y the
+// slot: the chunk's tile partials, summed in a fixed order (strided over the
+// lanes, then a butterfly).  A chunk holds at most kChunkTiles = 1024 tiles, 16
+// per lane; problems of thousands of small tensors have as many one-tile
+// chunks, which would otherwise cost a block each.
 constexpr int kChunksPerBlock = kBlock / 64;
 __global__ void __launch_bounds__(kBlock) k_reduce_chunks(ReduceParams r) {
-    int32_t p_t;
-    SchedState st;
-    if (!reduce_due(r, &p_t, &st) && !r.traced) return;
+    const int slot = blockIdx.y;
+    int j;
+    bool due;
+    if (!slot_step(r, span_plan(r.when, r.sched, r.rule), slot, &j, &due)) return;
     const int lane = threadIdx.x & 63;
     const int64_t ci = ((int64_t)r.block0 + blockIdx.x) * kChunksPerBlock + (threadIdx.x >> 6);
     if (ci >= r.n_chunks) return;  // whole waves: no block-wide barrier follows
+    const double *tp = r.tile_partials + slot * r.tile_stride;
     const Chunk c = r.chunks[ci];
     double a = 0.0, b = 0.0;
     if (c.count <= 64) {  // uniform over the wave: one tile partial per lane at most
         if (lane < c.count) {
-            a = r.tile_partials[2 * (int64_t)(c.first + lane)];
-            b = r.tile_partials[2 * (int64_t)(c.first + lane) + 1];
+            a = tp[2 * (int64_t)(c.first + lane)];
+            b = tp[2 * (int64_t)(c.first + lane) + 1];
         }
     } else {
         // all of a lane's loads are issued before the first add; the sum is
@@ -676,16 +927,16 @@ __global__ void __launch_bounds__(kBlock) k_reduce_chunks(ReduceParams r) {
         static_assert(kPerLane * 64 == kChunkTiles, "chunk tiles per lane");
         double va[kPerLane], vb[kPerLane];
 #pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
-            const int32_t i = lane + 64 * j;
-            const bool in_chunk = i < c.count;
-            va[j] = in_chunk ? r.tile_partials[2 * (int64_t)(c.first + i)] : 0.0;
-            vb[j] = in_chunk ? r.tile_partials[2 * (int64_t)(c.first + i) + 1] : 0.0;
+        for (int i = 0; i < kPerLane; ++i) {
+            const int32_t k = lane + 64 * i;
+            const bool in_chunk = k < c.count;
+            va[i] = in_chunk ? tp[2 * (int64_t)(c.first + k)] : 0.0;
+            vb[i] = in_chunk ? tp[2 * (int64_t)(c.first + k) + 1] : 0.0;
         }
 #pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
-            a += va[j];
-            b += vb[j];
+        for (int i = 0; i < kPerLane; ++i) {
+            a += va[i];
+            b += vb[i];
         }
     }
 #pragma unroll
@@ -694,48 +945,54 @@ __global__ void __launch_bounds__(kBlock) k_reduce_chunks(ReduceParams r) {
         b += __shfl_xor(b, off, 64);
     }
     if (lane == 0) {
-        r.chunk_partials[2 * ci] = a;
-        r.chunk_partials[2 * ci + 1] = b;
+        r.chunk_partials[slot * r.chunk_stride + 2 * ci] = a;
+        r.chunk_partials[slot * r.chunk_stride + 2 * ci + 1] = b;
     }
 }
 
 constexpr int kFinishThreads = 256;
+constexpr int kFinishTensors = 512;   // tensors whose sums the finishing block keeps in LDS
 
 // Level 2 for problems with more chunk partials than one LDS window: one block
-// per window of tensors.  A window of small tensors loads its chunk partials
-// (at most kFinishWindow) into LDS and gives each tensor to a thread, which
-// adds its chunks in a fixed order (four interleaved partial sums); a window
-// holding one large tensor adds its chunks strided over the block.  Writes
-// out[tau] = variance (deviation sum / K) and out[T + tau] = gradient norm^2
-// for its tensors, and the window's sums in a fixed order to win_partials.
+// per window of tensors (blockIdx.x) and slot (blockIdx.y).  A window of small
+// tensors loads its chunk partials (at most kFinishWindow) into LDS and gives
+// each tensor to a thread, which adds its chunks in a fixed order (four
+// interleaved partial sums); a window holding one large tensor adds its chunks
+// strided over the block.  Writes out[tau] = variance (deviation sum / K) and
+// out[T + tau] = gradient norm^2 for its tensors, and the window's sums in a
+// fixed order to win_partials.
 __global__ void __launch_bounds__(kFinishThreads) k_reduce_windows(ReduceParams r) {
     __shared__ double la[kFinishWindow], lb[kFinishWindow];
-    int32_t p_t;
-    SchedState st;
-    if (!reduce_due(r, &p_t, &st) && !r.traced) return;
+    const int slot = blockIdx.y;
+    int j;
+    bool due;
+    if (!slot_step(r, span_plan(r.when, r.sched, r.rule), slot, &j, &due)) return;
+    const double *cp = r.chunk_partials + slot * r.chunk_stride;
+    double *wp = r.win_partials + (int64_t)slot * 2 * r.n_windows;
+    double *out = reinterpret_cast<double *>(reinterpret_cast<char *>(slot_hdr(r, slot)) + kSlotHdrBytes);
     const int32_t w = blockIdx.x;
     const int32_t t0 = r.win_begin[w], t1 = r.win_begin[w + 1];
     const int32_t c0 = r.chunk_begin[t0], c1 = r.chunk_begin[t1];
     if (t1 == t0 + 1 && c1 - c0 > kSmallTensorChunks) {  // one large tensor
         double a = 0.0, g = 0.0;
         for (int32_t i = c0 + (int32_t)threadIdx.x; i < c1; i += kFinishThreads) {
-            a += r.chunk_partials[2 * (int64_t)i];
-            g += r.chunk_partials[2 * (int64_t)i + 1];
+            a += cp[2 * (int64_t)i];
+            g += cp[2 * (int64_t)i + 1];
         }
         const Pair tot = block_sum2<kFinishThreads / 64>(a, g);
         if (threadIdx.x == 0) {
             const double v = tot.a / (double)r.K;
-            r.out[t0] = v;
-            r.out[r.T + t0] = tot.b;
-            r.win_partials[2 * w] = v;
-            r.win_partials[2 * w + 1] = tot.b;
+            out[t0] = v;
+            out[r.T + t0] = tot.b;
+            wp[2 * w] = v;
+            wp[2 * w + 1] = tot.b;
         }
         return;
     }
     const int32_t n = c1 - c0;  // <= kFinishWindow (the host cut the window so)
     for (int32_t i = (int32_t)threadIdx.x; i < n; i += kFinishThreads) {
-        la[i] = r.chunk_partials[2 * (int64_t)(c0 + i)];
-        lb[i] = r.chunk_partials[2 * (int64_t)(c0 + i) + 1];
+        la[i] = cp[2 * (int64_t)(c0 + i)];
+        lb[i] = cp[2 * (int64_t)(c0 + i) + 1];
     }
     __syncthreads();
     double sa = 0.0, sb = 0.0;
@@ -745,9 +1002,9 @@ __global__ void __launch_bounds__(kFinishThreads) k_reduce_windows(ReduceParams 
         int32_t i = b;
         for (; i + 4 <= e; i += 4) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                a[j] += la[i + j];
-                g[j] += lb[i + j];
+            for (int q = 0; q < 4; ++q) {
+                a[q] += la[i + q];
+                g[q] += lb[i + q];
             }
         }
         if (i < e) { a[0] += la[i]; g[0] += lb[i]; }
@@ -755,56 +1012,71 @@ __global__ void __launch_bounds__(kFinishThreads) k_reduce_windows(ReduceParams 
         if (i + 2 < e) { a[2] += la[i + 2]; g[2] += lb[i + 2]; }
         const double v = e > b ? ((a[0] + a[1]) + (a[2] + a[3])) / (double)r.K : 0.0;
         const double gn = e > b ? (g[0] + g[1]) + (g[2] + g[3]) : 0.0;
-        r.out[tau] = v;
-        r.out[r.T + tau] = gn;
+        out[tau] = v;
+        out[r.T + tau] = gn;
         sa += v;
         sb += gn;
     }
     const Pair tot = block_sum2<kFinishThreads / 64>(sa, sb);
     if (threadIdx.x == 0) {
-        r.win_partials[2 * w] = tot.a;
-        r.win_partials[2 * w + 1] = tot.b;
+        wp[2 * w] = tot.a;
+        wp[2 * w + 1] = tot.b;
     }
 }
 
-// Level 2 and the decision, one block.  With at most kFinishWindow chunk
-// partials (n_windows = 0) it sums the tensors itself, in a fixed order chosen
-// by the tensor's chunk count: a tensor of at most kSmallTensorChunks chunks is
-// owned by one thread, which adds its chunks from LDS (four interleaved partial
-// sums); a larger tensor is owned by one wave, whose lanes add strided chunks
-// from LDS before a butterfly; then out[tau] = variance (deviation sum / K),
-// out[T + tau] = gradient norm^2, and S and the norm total are block sums.
-// Otherwise k_reduce_windows has written out, and S and the norm total are
-// block sums of its window partials.  With a schedule, thread 0 then applies
-// Algorithm 2's sampling and period decision (the same apply_sync as the host
-// controller) and
-// writes the new state.  out and the record header are the host's pinned
-// record slot, written directly; the header is written in every case.
+// Level 2 and the decision, one block per slot.  With at most kFinishWindow
+// chunk partials (n_windows = 0) it sums the tensors itself, in a fixed order
+// chosen by the tensor's chunk count: a tensor of at most kSmallTensorChunks
+// chunks is owned by one thread, which adds its chunks from LDS (four
+// interleaved partial sums); a larger tensor is owned by one wave, whose lanes
+// add strided chunks from LDS before a butterfly; then out[tau] = variance
+// (deviation sum / K), out[T + tau] = gradient norm^2, and S and the norm total
+// are block sums.  Otherwise k_reduce_windows has written out, and S and the
+// norm total are block sums of its window partials.  With a controller on the
+// device and one slot, thread 0 then takes Algorithm 2's decision; with several
+// slots it leaves the sums to k_control, which takes them in step order; with
+// none it writes the record itself, nothing of which moves at a sync.  out and
+// the record header are the host's pinned record slot, written directly.
 __global__ void __launch_bounds__(kFinishThreads) k_reduce_finish(ReduceParams r) {
     __shared__ double la[kFinishWindow], lb[kFinishWindow];
-    int32_t p_t;
-    SchedState st;
-    const bool due = reduce_due(r, &p_t, &st);
-    if (!due && !r.traced) {
-        if (threadIdx.x == 0) write_hdr(r, 0, p_t, p_t, ADPSGD_OK, 0.0, 0.0, st);
+    __shared__ double lacc[2 * kFinishTensors];   // per-tensor sums, where they fit
+    const int slot = blockIdx.x;
+    fetch_args<offsetof(ReduceParams, gamma)>();
+    if (r.n_windows == 0) {
+        // every chunk partial fits one LDS window (the host cuts the tensors into
+        // windows for k_reduce_windows otherwise); the loads are under way while
+        // the plan is worked out (of a slot without a measurement they are not used)
+        const double *cp = r.chunk_partials + slot * r.chunk_stride;
+        for (int32_t i = (int32_t)threadIdx.x; i < r.n_chunks; i += kFinishThreads) {
+            la[i] = cp[2 * (int64_t)i];
+            lb[i] = cp[2 * (int64_t)i + 1];
+        }
+    }
+    const SpanPlan sp = span_plan(r.when, r.sched, r.rule);
+    int j;
+    bool due;
+    if (!slot_step(r, sp, slot, &j, &due)) {
+        __syncthreads();   // every thread has read the controller state
+        if (threadIdx.x == 0 && r.n_slots == 1 && r.control) {
+            SchedState st = *r.sched;
+            write_hdr(slot_hdr(r, 0), sp.t + sp.n - 1, sp.n, false, st.p, st.p, ADPSGD_OK, 0.0, 0.0, st.C2, st.nC2);
+            end_span(r, sp, &st);
+            *r.sched = st;
+        }
         return;
     }
+    double *out = reinterpret_cast<double *>(reinterpret_cast<char *>(slot_hdr(r, slot)) + kSlotHdrBytes);
     double sa = 0.0, sb = 0.0;
     if (r.n_windows > 0) {
         // the tensors were reduced by k_reduce_windows: add the window sums
+        const double *wp = r.win_partials + (int64_t)slot * 2 * r.n_windows;
         for (int32_t w = (int32_t)threadIdx.x; w < r.n_windows; w += kFinishThreads) {
-            sa += r.win_partials[2 * w];
-            sb += r.win_partials[2 * w + 1];
+            sa += wp[2 * w];
+            sb += wp[2 * w + 1];
         }
     } else {
-        // every chunk partial fits one LDS window (the host cuts the tensors
-        // into windows for k_reduce_windows otherwise)
-        const int32_t n = r.n_chunks;
-        for (int32_t i = (int32_t)threadIdx.x; i < n; i += kFinishThreads) {
-            la[i] = r.chunk_partials[2 * (int64_t)i];
-            lb[i] = r.chunk_partials[2 * (int64_t)i + 1];
-        }
-        __syncthreads();
+        double *acc = r.T <= kFinishTensors ? lacc : r.acc + (int64_t)slot * 2 * r.T;
+        __syncthreads();   // la, lb
         // small tensors: a thread each
         for (int32_t tau = (int32_t)threadIdx.x; tau < r.T; tau += kFinishThreads) {
             const int32_t b = r.chunk_begin[tau], e = r.chunk_begin[tau + 1];
@@ -813,22 +1085,22 @@ __global__ void __launch_bounds__(kFinishThreads) k_reduce_finish(ReduceParams r
             int32_t i = b;
             for (; i + 4 <= e; i += 4) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    a[j] += la[i + j];
-                    g[j] += lb[i + j];
+                for (int q = 0; q < 4; ++q) {
+                    a[q] += la[i + q];
+                    g[q] += lb[i + q];
                 }
             }
             if (i < e) { a[0] += la[i]; g[0] += lb[i]; }
             if (i + 1 < e) { a[1] += la[i + 1]; g[1] += lb[i + 1]; }
             if (i + 2 < e) { a[2] += la[i + 2]; g[2] += lb[i + 2]; }
-            r.acc[tau] = (a[0] + a[1]) + (a[2] + a[3]);
-            r.acc[r.T + tau] = (g[0] + g[1]) + (g[2] + g[3]);
+            acc[tau] = (a[0] + a[1]) + (a[2] + a[3]);
+            acc[r.T + tau] = (g[0] + g[1]) + (g[2] + g[3]);
         }
         // large tensors (listed by the host): a wave each, strided lanes, then
         // a butterfly
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        for (int32_t j = wave; j < r.n_large; j += kFinishThreads / 64) {
-            const int32_t tau = r.large[j];
+        for (int32_t k = wave; k < r.n_large; k += kFinishThreads / 64) {
+            const int32_t tau = r.large[k];
             const int32_t cb = r.chunk_begin[tau], ce = r.chunk_begin[tau + 1];
             double a = 0.0, g = 0.0;
             for (int32_t i = cb + lane; i < ce; i += 64) {
@@ -841,36 +1113,55 @@ __global__ void __launch_bounds__(kFinishThreads) k_reduce_finish(ReduceParams r
                 g += __shfl_xor(g, off, 64);
             }
             if (lane == 0) {
-                r.acc[tau] = a;
-                r.acc[r.T + tau] = g;
+                acc[tau] = a;
+                acc[r.T + tau] = g;
             }
         }
         __syncthreads();  // acc of the large tensors, for their owner threads below
         for (int32_t tau = (int32_t)threadIdx.x; tau < r.T; tau += kFinishThreads) {
             double v = 0.0, g = 0.0;
             if (r.chunk_begin[tau + 1] > r.chunk_begin[tau]) {
-                v = r.acc[tau] / (double)r.K;
-                g = r.acc[r.T + tau];
+                v = acc[tau] / (double)r.K;
+                g = acc[r.T + tau];
             }
-            r.out[tau] = v;
-            r.out[r.T + tau] = g;
+            out[tau] = v;
+            out[r.T + tau] = g;
             sa += v;
             sb += g;
         }
     }
     const Pair tot = block_sum2<kFinishThreads / 64>(sa, sb);
     if (threadIdx.x == 0) {
-        int32_t status = ADPSGD_OK, p_next = p_t;
-        if (r.sched && due) {
-            st.p = p_t;
-            // a non-finite S restarts the counter and moves nothing else
-            if (!apply_sync(r.rule, r.t, r.gamma, tot.a, &st, nullptr)) status = ADPSGD_ENONFINITE;
-            st.t = r.t + 1;
+        if (r.control && r.n_slots == 1) {
+            SchedState st = *r.sched;
+            control_slot(r, sp, 0, j, due, tot.a, tot.b, &st);
+            end_span(r, sp, &st);
             *r.sched = st;
-            p_next = st.p;
+        } else if (r.control) {
+            r.sums[2 * slot] = tot.a;
+            r.sums[2 * slot + 1] = tot.b;
+        } else {
+            const int64_t t = sp.t + j;
+            const int32_t p_t = period_at(r.rule, r.st0.p, t);
+            write_hdr(slot_hdr(r, slot), t, sp.n, due, p_t, p_t,
+                      __builtin_isfinite(tot.a) ? ADPSGD_OK : ADPSGD_ENONFINITE, tot.a, tot.b, r.st0.C2, r.st0.nC2);
         }
-        write_hdr(r, due ? 1 : 0, p_t, p_next, status, tot.a, tot.b, st);
     }
+}
+
+// The decisions of a launch of several measurements, in step order (one thread).
+__global__ void __launch_bounds__(64) k_control(ReduceParams r) {
+    if (threadIdx.x != 0) return;
+    SchedState st = *r.sched;
+    const SpanPlan sp = span_plan(r.when, r.sched, r.rule);
+    int j;
+    bool due;
+    for (int slot = 0; slot < r.n_slots && slot_step(r, sp, slot, &j, &due); ++slot)
+        control_slot(r, sp, slot, j, due, r.sums[2 * slot], r.sums[2 * slot + 1], &st);
+    if (!slot_step(r, sp, 0, &j, &due))
+        write_hdr(slot_hdr(r, 0), sp.t + sp.n - 1, sp.n, false, st.p, st.p, ADPSGD_OK, 0.0, 0.0, st.C2, st.nC2);
+    end_span(r, sp, &st);
+    *r.sched = st;
 }
 
 // ---------------------------------------------------------------- problem data
@@ -964,79 +1255,83 @@ size_t static_lds_of(Kern kern) {
     return hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(kern)) == hipSuccess ? fa.sharedSizeBytes : 0;
 }
 
-// Does the K-argument sync-tile kernel take K in this mode (else the loop
-// kernel does)?  Two rows per wave up to K = 32 and four up to 64 (the last
-// wave of a K that is not a multiple holds fewer): a CU holds at most two
-// blocks of 9-16 waves, and several rows per wave keep more bytes in flight.
-// K = 3 is the exception: one row per wave in the modes with a step, and the
-// loop kernel for the separate sync (76% of peak, against 58% and 48% for
-// three one-row or two two-row waves); both add the rows in row order, so the
-// replicas keep the same bits.
-constexpr bool any_k_kernel(int K, int mode) {
-    if (K == 3) return mode != kAverage;
-    return K > 0 && K <= 64;
+// Does the K-argument sync kernel take K (else the loop kernel does)?  Two rows
+// per wave up to K = 32, four up to 64 and eight up to 128 (the last wave of a
+// K that is not a multiple holds fewer): a CU holds at most two blocks of 9-16
+// waves, and several rows per wave keep more bytes in flight.  K = 3 is the
+// exception: one row per wave in a span, and the loop kernel for the separate
+// sync (76% of peak, against 58% and 48% for three one-row or two two-row
+// waves); both add the rows in row order, so the replicas keep the same bits.
+constexpr bool any_k_kernel(int K, bool average) {
+    if (K == 3) return !average;
+    return K > 0 && K <= kMaxRegisterK;
 }
-constexpr int any_k_rows(int K) { return K == 3 ? 1 : (K <= 32 ? 2 : 4); }
+constexpr int any_k_rows(int K) { return K == 3 ? 1 : (K <= 32 ? 2 : (K <= 64 ? 4 : 8)); }
 constexpr int any_k_waves(int K) { return (K + any_k_rows(K) - 1) / any_k_rows(K); }
 
-template <int KT, bool VEC, bool NT, int MODE, bool AVGM, int RD, bool RAGGED>
-hipError_t sync_variant(const SyncParams &p, int64_t, int cap, hipStream_t st) {
-    const int threads = KT > 0 ? 64 * sync_waves<KT, MODE>() : 64 * any_k_waves(p.s.K);
+template <int KT, bool VEC, bool NT, bool AVGM, int RD, bool RAGGED>
+hipError_t average_variant(const SyncParams &p, int cap, hipStream_t st) {
+    const int threads = KT > 0 ? 64 * average_waves<KT>() : 64 * any_k_waves(p.s.K);
     int lds = 0;
     if (cap > 0) {   // (the attribute query only when it is needed: not under graph capture)
-        static const size_t own = static_lds_of(k_sync_lds<KT, VEC, NT, MODE, AVGM, RD, RAGGED>);
+        static const size_t own = static_lds_of(k_average<KT, VEC, NT, AVGM, RD, RAGGED>);
         lds = cap_lds(cap, own);
     }
     return in_pieces(p.n_chunks, threads, [&](int64_t b0, unsigned nb) {   // a block per chunk
         SyncParams q = p;
         q.s.block0 = b0;
-        k_sync_lds<KT, VEC, NT, MODE, AVGM, RD, RAGGED><<<dim3(nb), dim3(threads), lds, st>>>(q);
+        k_average<KT, VEC, NT, AVGM, RD, RAGGED><<<dim3(nb), dim3(threads), lds, st>>>(q);
     });
-}
-
-template <int KT, int MODE, bool AVGM, int RD, bool RAGGED>
-hipError_t sync_dispatch(const SyncParams &p, int64_t n_tiles, bool vec, bool nt, int cap, hipStream_t st) {
-    if (vec && nt) return sync_variant<KT, true, true, MODE, AVGM, RD, RAGGED>(p, n_tiles, cap, st);
-    if (vec) return sync_variant<KT, true, false, MODE, AVGM, RD, RAGGED>(p, n_tiles, cap, st);
-    return sync_variant<KT, false, false, MODE, AVGM, RD, RAGGED>(p, n_tiles, cap, st);
 }
 
 template <int KT, int RD = 0, bool RAGGED = false>
-hipError_t sync_dispatch(const SyncParams &p, int64_t n_tiles, int mode, bool avg_m, bool vec, bool nt, int cap,
-                         hipStream_t st) {
-    switch (mode) {
-    case kAverage: return avg_m ? sync_dispatch<KT, kAverage, true, RD, RAGGED>(p, n_tiles, vec, nt, cap, st)
-                                : sync_dispatch<KT, kAverage, false, RD, RAGGED>(p, n_tiles, vec, nt, cap, st);
-    case kFused: return avg_m ? sync_dispatch<KT, kFused, true, RD, RAGGED>(p, n_tiles, vec, nt, cap, st)
-                              : sync_dispatch<KT, kFused, false, RD, RAGGED>(p, n_tiles, vec, nt, cap, st);
-    case kDevice: return avg_m ? sync_dispatch<KT, kDevice, true, RD, RAGGED>(p, n_tiles, vec, nt, cap, st)
-                               : sync_dispatch<KT, kDevice, false, RD, RAGGED>(p, n_tiles, vec, nt, cap, st);
-    default: return avg_m ? sync_dispatch<KT, kDeviceTrace, true, RD, RAGGED>(p, n_tiles, vec, nt, cap, st)
-                          : sync_dispatch<KT, kDeviceTrace, false, RD, RAGGED>(p, n_tiles, vec, nt, cap, st);
+hipError_t average_dispatch(const SyncParams &p, bool avg_m, bool vec, bool nt, int cap, hipStream_t st) {
+    if (avg_m) {
+        if (vec && nt) return average_variant<KT, true, true, true, RD, RAGGED>(p, cap, st);
+        if (vec) return average_variant<KT, true, false, true, RD, RAGGED>(p, cap, st);
+        return average_variant<KT, false, false, true, RD, RAGGED>(p, cap, st);
     }
+    if (vec && nt) return average_variant<KT, true, true, false, RD, RAGGED>(p, cap, st);
+    if (vec) return average_variant<KT, true, false, false, RD, RAGGED>(p, cap, st);
+    return average_variant<KT, false, false, false, RD, RAGGED>(p, cap, st);
 }
 
-template <int MODE, bool AVGM>
-hipError_t loop_dispatch(const SyncParams &p, int64_t n_tiles, bool vec, hipStream_t st) {
-    return in_pieces(n_tiles, 64, [&](int64_t b0, unsigned nb) {
-        SyncParams q = p;
+template <int KT, int R>
+hipError_t span_variant(const SpanParams &p, bool vec, bool nt, hipStream_t st) {
+    const int threads = KT > 0 ? 64 * span_waves<KT, R>() : 64 * any_k_waves(p.s.K);
+    return in_pieces(p.n_chunks, threads, [&](int64_t b0, unsigned nb) {   // a block per chunk
+        SpanParams q = p;
         q.s.block0 = b0;
-        if (vec) k_sync_loop<true, MODE, AVGM><<<dim3(nb), dim3(64), 0, st>>>(q);
-        else k_sync_loop<false, MODE, AVGM><<<dim3(nb), dim3(64), 0, st>>>(q);
+        if (vec && nt) k_span<KT, R, true, true><<<dim3(nb), dim3(threads), 0, st>>>(q);
+        else if (vec) k_span<KT, R, true, false><<<dim3(nb), dim3(threads), 0, st>>>(q);
+        else k_span<KT, R, false, false><<<dim3(nb), dim3(threads), 0, st>>>(q);
     });
 }
 
-hipError_t loop_dispatch(const SyncParams &p, int64_t n_tiles, int mode, bool avg_m, bool vec, hipStream_t st) {
-    switch (mode) {
-    case kAverage: return avg_m ? loop_dispatch<kAverage, true>(p, n_tiles, vec, st)
-                                : loop_dispatch<kAverage, false>(p, n_tiles, vec, st);
-    case kFused: return avg_m ? loop_dispatch<kFused, true>(p, n_tiles, vec, st)
-                              : loop_dispatch<kFused, false>(p, n_tiles, vec, st);
-    case kDevice: return avg_m ? loop_dispatch<kDevice, true>(p, n_tiles, vec, st)
-                               : loop_dispatch<kDevice, false>(p, n_tiles, vec, st);
-    default: return avg_m ? loop_dispatch<kDeviceTrace, true>(p, n_tiles, vec, st)
-                          : loop_dispatch<kDeviceTrace, false>(p, n_tiles, vec, st);
-    }
+// A compiled K runs a span in one of two layouts.  One row per wave (two at K =
+// 32) streams best and has the most waves; several rows per wave share the
+// lanes' Philox products and the work of a sync.  Measured for 1 / 2 / 3 / 4 / 8
+// steps with a sync at the end: K = 8, P = 138M 3.09 / 3.13 / 3.32 / 3.63 / 5.45
+// ms with one row, 3.28 / 3.27 / 3.25 / 3.24 / 5.02 with two; K = 16, P = 25.6M
+// 1.12 / 1.14 / 1.27 / 1.39 / 2.06 and 1.20 / 1.20 / 1.21 / 1.20 / 1.83 (four
+// rows).  So from three steps on the taller layout, and at K = 32 always (104
+// against 107 us), unless its waves would not give every SIMD two: 64 steps with
+// 8 syncs at K = 4, P = 65,536 take 19 us in 1024 one-row waves, 29 in 512.
+template <int KT, int WIDE, int TALL>
+hipError_t span_dispatch(const SpanParams &p, bool vec, bool nt, hipStream_t st) {
+    const bool fills = p.n_chunks * span_waves<KT, TALL>() >= 2 * kSimds;
+    if (fills && (p.when.n >= 3 || KT == 32)) return span_variant<KT, TALL>(p, vec, nt, st);
+    return span_variant<KT, WIDE>(p, vec, nt, st);
+}
+
+template <bool STEP>
+hipError_t loop_variant(const SpanParams &p, int64_t n_tiles, bool vec, hipStream_t st) {
+    return in_pieces(n_tiles, 64, [&](int64_t b0, unsigned nb) {
+        SpanParams q = p;
+        q.s.block0 = b0;
+        if (vec) k_sync_loop<true, STEP><<<dim3(nb), dim3(64), 0, st>>>(q);
+        else k_sync_loop<false, STEP><<<dim3(nb), dim3(64), 0, st>>>(q);
+    });
 }
 
 }  // namespace
@@ -1077,41 +1372,101 @@ hipError_t launch_local_step(const StepParams &p, bool vec, bool nt, const StepS
     }
 }
 
-int sync_tile_waves(int K, int mode) {
-    const bool avg = mode == kAverage;
+int average_tile_waves(int K) {
     switch (K) {
-    case 1: return avg ? sync_waves<1, kAverage>() : sync_waves<1, kFused>();
-    case 2: return avg ? sync_waves<2, kAverage>() : sync_waves<2, kFused>();
-    case 4: return avg ? sync_waves<4, kAverage>() : sync_waves<4, kFused>();
-    case 8: return avg ? sync_waves<8, kAverage>() : sync_waves<8, kFused>();
-    case 16: return avg ? sync_waves<16, kAverage>() : sync_waves<16, kFused>();
-    case 32: return avg ? sync_waves<32, kAverage>() : sync_waves<32, kFused>();
-    default: return any_k_kernel(K, mode) ? any_k_waves(K) : 0;
+    case 1: return average_waves<1>();
+    case 2: return average_waves<2>();
+    case 4: return average_waves<4>();
+    case 8: return average_waves<8>();
+    case 16: return average_waves<16>();
+    case 32: return average_waves<32>();
+    default: return any_k_kernel(K, true) ? any_k_waves(K) : 0;
     }
 }
 
-hipError_t launch_tile_sync(const SyncParams &p, int64_t n_tiles, int mode, bool avg_m, bool vec, bool nt,
-                            int cap, hipStream_t st) {
+hipError_t launch_average(const SyncParams &p, int64_t n_tiles, bool avg_m, bool vec, bool nt, int cap,
+                          hipStream_t st) {
     if (n_tiles <= 0) return hipSuccess;
-    switch (p.s.K) {
-    case 1: return sync_dispatch<1>(p, n_tiles, mode, avg_m, vec, nt, cap, st);
-    case 2: return sync_dispatch<2>(p, n_tiles, mode, avg_m, vec, nt, cap, st);
-    case 4: return sync_dispatch<4>(p, n_tiles, mode, avg_m, vec, nt, cap, st);
-    case 8: return sync_dispatch<8>(p, n_tiles, mode, avg_m, vec, nt, cap, st);
-    case 16: return sync_dispatch<16>(p, n_tiles, mode, avg_m, vec, nt, cap, st);
-    case 32: return sync_dispatch<32>(p, n_tiles, mode, avg_m, vec, nt, cap, st);
-    default:
-        if (!any_k_kernel(p.s.K, mode)) return loop_dispatch(p, n_tiles, mode, avg_m, vec, st);
-        switch (any_k_rows(p.s.K)) {
-        case 1: return sync_dispatch<0, 1, false>(p, n_tiles, mode, avg_m, vec, nt, cap, st);
-        case 2:
-            return p.s.K % 2 == 0 ? sync_dispatch<0, 2, false>(p, n_tiles, mode, avg_m, vec, nt, cap, st)
-                                  : sync_dispatch<0, 2, true>(p, n_tiles, mode, avg_m, vec, nt, cap, st);
-        default:
-            return p.s.K % 4 == 0 ? sync_dispatch<0, 4, false>(p, n_tiles, mode, avg_m, vec, nt, cap, st)
-                                  : sync_dispatch<0, 4, true>(p, n_tiles, mode, avg_m, vec, nt, cap, st);
+    const int K = p.s.K;
+    switch (K) {
+    case 1: return average_dispatch<1>(p, avg_m, vec, nt, cap, st);
+    case 2: return average_dispatch<2>(p, avg_m, vec, nt, cap, st);
+    case 4: return average_dispatch<4>(p, avg_m, vec, nt, cap, st);
+    case 8: return average_dispatch<8>(p, avg_m, vec, nt, cap, st);
+    case 16: return average_dispatch<16>(p, avg_m, vec, nt, cap, st);
+    case 32: return average_dispatch<32>(p, avg_m, vec, nt, cap, st);
+    default: break;
+    }
+    if (!any_k_kernel(K, true)) {
+        SpanParams q{};
+        static_cast<SyncParams &>(q) = p;
+        q.avg_m = avg_m ? 1 : 0;
+        return loop_variant<false>(q, n_tiles, vec, st);
+    }
+    switch (any_k_rows(K)) {
+    case 2:
+        return K % 2 == 0 ? average_dispatch<0, 2, false>(p, avg_m, vec, nt, cap, st)
+                          : average_dispatch<0, 2, true>(p, avg_m, vec, nt, cap, st);
+    case 4:
+        return K % 4 == 0 ? average_dispatch<0, 4, false>(p, avg_m, vec, nt, cap, st)
+                          : average_dispatch<0, 4, true>(p, avg_m, vec, nt, cap, st);
+    default: return average_dispatch<0, 8, true>(p, avg_m, vec, nt, cap, st);
+    }
+}
+
+bool span_in_registers(int K) { return K <= kMaxRegisterK; }
+
+hipError_t launch_span(const SpanParams &p, int64_t n_tiles, bool vec, bool nt, bool step_nt, const StepShape &shape,
+                       hipStream_t st) {
+    if (p.when.n < 1 || p.when.n > kSpanSteps) return hipErrorInvalidValue;
+    if (n_tiles <= 0) return hipSuccess;
+    const int K = p.s.K;
+    switch (K) {
+    case 1: return span_variant<1, 1>(p, vec, nt, st);
+    case 2: return span_dispatch<2, 1, 2>(p, vec, nt, st);
+    case 4: return span_dispatch<4, 1, 2>(p, vec, nt, st);
+    case 8: return span_dispatch<8, 1, 2>(p, vec, nt, st);
+    case 16: return span_dispatch<16, 1, 4>(p, vec, nt, st);
+    case 32: return span_dispatch<32, 2, 4>(p, vec, nt, st);
+    default: break;
+    }
+    if (any_k_kernel(K, false)) {
+        switch (any_k_rows(K)) {
+        case 1: return span_variant<0, 1>(p, vec, nt, st);
+        case 2: return span_variant<0, 2>(p, vec, nt, st);
+        case 4: return span_variant<0, 4>(p, vec, nt, st);
+        default: return span_variant<0, 8>(p, vec, nt, st);
         }
     }
+    // too many workers for the registers: the steps before each measured one in
+    // one launch, then that step with the loop kernel (a span that the device
+    // ends is one step here)
+    if (p.when.device) return p.when.n == 1 ? loop_variant<true>(p, n_tiles, vec, st) : hipErrorInvalidValue;
+    int slot = 0;
+    for (int j = 0; j < p.when.n;) {
+        int to = j;
+        while (to < p.when.n && !p.when.measure && !((p.when.syncs >> to) & 1)) ++to;
+        SpanParams q = p;
+        auto from = [&](int first, int n) {   // q's steps: first .. first + n - 1 of the span
+            q.s.t = p.s.t + (uint32_t)first;
+            q.s.n = n;
+            std::copy(p.s.gamma + first, p.s.gamma + first + n, q.s.gamma);
+        };
+        if (to > j) {
+            from(j, to - j);
+            if (const hipError_t e = launch_local_step(q.s, vec, step_nt, shape, st)) return e;
+        }
+        if (to < p.when.n) {
+            from(to, 1);
+            q.when.t = p.when.t + to;
+            q.when.n = 1;
+            q.when.syncs = (p.when.syncs >> to) & 1;
+            q.partials = p.partials + (int64_t)slot++ * p.slot_stride;
+            if (const hipError_t e = loop_variant<true>(q, n_tiles, vec, st)) return e;
+        }
+        j = to + 1;
+    }
+    return hipSuccess;
 }
 
 bool chunk_segments(const std::vector<Tile> &tiles, int64_t n_chunks, std::vector<int32_t> *out) {
@@ -1130,21 +1485,25 @@ bool chunk_segments(const std::vector<Tile> &tiles, int64_t n_chunks, std::vecto
 }
 
 hipError_t launch_reduce(const ReduceParams &r, hipStream_t st) {
+    const unsigned slots = (unsigned)r.n_slots;
     if (r.n_chunks > 0 && !r.chunks_are_tiles) {
         const int64_t blocks = (r.n_chunks + kChunksPerBlock - 1) / kChunksPerBlock;
         const hipError_t e = in_pieces(blocks, kBlock, [&](int64_t b0, unsigned nb) {
             ReduceParams q = r;
             q.block0 = (int32_t)b0;
-            k_reduce_chunks<<<dim3(nb), dim3(kBlock), 0, st>>>(q);
+            k_reduce_chunks<<<dim3(nb, slots), dim3(kBlock), 0, st>>>(q);
         });
         if (e != hipSuccess) return e;
     }
     if (r.n_windows > 0) {
-        k_reduce_windows<<<dim3((unsigned)r.n_windows), dim3(kFinishThreads), 0, st>>>(r);
+        k_reduce_windows<<<dim3((unsigned)r.n_windows, slots), dim3(kFinishThreads), 0, st>>>(r);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    k_reduce_finish<<<dim3(1), dim3(kFinishThreads), 0, st>>>(r);
+    k_reduce_finish<<<dim3(slots), dim3(kFinishThreads), 0, st>>>(r);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !r.control || slots == 1) return e;
+    k_control<<<dim3(1), dim3(64), 0, st>>>(r);
     return hipGetLastError();
 }
 

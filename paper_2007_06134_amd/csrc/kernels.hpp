@@ -41,9 +41,6 @@ struct Chunk {
     int32_t pad_;
 };
 
-// Local steps per launch at most: their rates travel in the kernel arguments.
-constexpr int kSpanSteps = 64;
-
 // Everything a local step needs.  Replicas are rows of x and m, ld elements apart.
 struct StepParams {
     float *x;
@@ -57,7 +54,7 @@ struct StepParams {
     uint32_t t;        // first step's index (Philox counter word 2)
     float sigma_r;     // sigma sqrt(2 ln 2) (see add_noise2)
     float mu, wd;
-    int32_t n;         // steps of this launch: t .. t + n - 1 (k_local_step; the sync kernels take one)
+    int32_t n;         // steps of this launch: t .. t + n - 1 (k_local_step; see SpanWhen for k_span)
     RoundKeys rk;
     // Chunks of one worker's row that an XCD takes one after another before
     // the next worker's (the local step's block order; set by
@@ -67,26 +64,33 @@ struct StepParams {
     // work-items, so larger grids go out as several launches (the launchers
     // below set it; callers leave it 0).
     int64_t block0;
-    float gamma[kSpanSteps];  // the rates of steps t .. t + n - 1
+    float gamma[kSpanSteps];  // the rates of steps t, t + 1, ...
 };
 
+// (The rates come last in every kernel's arguments, so that what all of its waves
+// read first lies together.)
 struct SyncParams {
-    StepParams s;      // x, m, P, K; the step fields are used by the modes with a step
     const Tile *tiles;
     double *partials;  // [2 n_tiles]: per tile, sum of sum_k (xbar - x_k)^2, gradient norm^2
-    // The sync-tile kernel (not the loop kernel) takes one block per aligned
+    // k_span and k_average (not the loop kernel) take one block per aligned
     // chunk of kTileElems elements, [c kTileElems, (c + 1) kTileElems) cut at P,
     // whatever tensors it holds: its tiles are chunk_seg[c] .. chunk_seg[c+1]-1
     // (every chunk holds at least one), so a tensor boundary inside a chunk
     // costs no block of its own.
     const int32_t *chunk_seg;  // [n_chunks + 1]
     int64_t n_chunks;          // ceil(P / kTileElems)
-    // modes decided on the device: step s.t syncs iff Algorithm 2's counter,
-    // read from *sched at block start, says so (the state is written only by
-    // the reduction kernel that follows a sync)
-    const SchedState *sched;
+    StepParams s;              // x, m, P, K; the step fields are used by spans
+};
+
+struct SpanControl {
+    int64_t slot_stride;       // doubles from one measurement's tile partials to the next's
+    const SchedState *sched;   // (when.device) the controller state
+    SpanWhen when;             // s.t = when.t, s.gamma[0] its rate
+    int32_t avg_m;             // 1: a sync also averages the momentum buffers
+    int32_t pad_;
     SchedRule rule;
 };
+struct SpanParams : SpanControl, SyncParams {};
 
 // Launch shapes of the local step: threads per block (= float4 groups per
 // block), an LDS reservation per block, and the block order.  The kernel uses
@@ -121,53 +125,55 @@ int64_t local_step_blocks(int64_t n_groups, int32_t K, const StepShape &shape);
 // row_chunks in [1, kMaxRowChunks]; p.n in [1, kSpanSteps] (hipErrorInvalidValue otherwise).
 hipError_t launch_local_step(const StepParams &p, bool vec, bool nontemporal, const StepShape &shape,
                              hipStream_t st);
-// What a sync-tile kernel does:
-//   kAverage      average only (a separate sync);
-//   kFused        one local step, then average (a period's last step);
-//   kDevice       one local step, then average iff a sync is due (decided on
-//                 the device); without a sync nothing is measured;
-//   kDeviceTrace  one local step, measure (variance and gradient norm at the
-//                 mean), then average iff a sync is due.
-enum SyncMode : int { kAverage = 0, kFused = 1, kDevice = 2, kDeviceTrace = 3 };
-
-// Tile partials are pairs (sum of squared deviations, squared gradient norm at
-// the mean; the latter only when tracing).  avg_m = true: a sync also averages
-// the momentum buffers.  cap > 0 reserves LDS (160 KB per CU on gfx950) so
-// that at most cap blocks of the sync-tile kernel are resident per CU; 0: none.
-// The loop kernel (K above 64, the separate sync at K = 3) ignores it.
-hipError_t launch_tile_sync(const SyncParams &p, int64_t n_tiles, int mode, bool avg_m, bool vec,
-                            bool nontemporal, int cap, hipStream_t st);
+// The synchronization alone.  avg_m: the momentum buffers too.  cap > 0 reserves
+// LDS (160 KB per CU on gfx950) so that at most cap blocks are resident per CU;
+// 0: none.  The loop kernel (K above 128, and K = 3) ignores nontemporal and cap.
+hipError_t launch_average(const SyncParams &p, int64_t n_tiles, bool avg_m, bool vec, bool nontemporal, int cap,
+                          hipStream_t st);
+// Workers whose replicas k_span and k_average hold in the registers of one block.
+constexpr int kMaxRegisterK = 128;
+constexpr int kSimds = 1024;   // of the 256 CUs
+// The span p.when.  With K above kMaxRegisterK a span that the device ends has
+// n = 1; a planned one goes out as plain steps (step_nt, shape as for
+// launch_local_step) and one loop kernel per measured step.
+bool span_in_registers(int K);
+hipError_t launch_span(const SpanParams &p, int64_t n_tiles, bool vec, bool nontemporal, bool step_nt,
+                       const StepShape &shape, hipStream_t st);
 // chunk_seg (SyncParams) of a tile table: out[c] = the first tile that starts in
 // chunk c, out[n_chunks] = n_tiles; false if some chunk holds no tile.
 bool chunk_segments(const std::vector<Tile> &tiles, int64_t n_chunks, std::vector<int32_t> *out);
-// Waves per block of the sync-tile kernel for K workers in a mode (0 when K
-// takes the loop kernel).
-int sync_tile_waves(int K, int mode);
+// Waves per block of the separate sync for K workers (0: K takes the loop kernel).
+int average_tile_waves(int K);
 constexpr int kLdsPerCU = 160 * 1024;
 // Resident waves per CU that the separate sync is timed with at init.
 constexpr int kAverageCapWaves = 24;
 
-// Record of one launch of the reduction kernel (one step or one sync).
+// Record of one measurement (or, in a launch that the device ended without one,
+// of the launch, in its first slot).
 struct SlotHdr {
-    int64_t t;        // the step (or the sync's step)
+    int64_t t;        // the measured step (the launch's last without a measurement)
     int32_t due;      // 1: a sync followed the step
     int32_t p;        // period in force for the step
     int32_t p_next;   // period after the sync's decision
     int32_t status;   // ADPSGD_OK, or ADPSGD_ENONFINITE when S was not finite
-    double S;         // sum over tensors of the variances (0 without a reduction)
+    double S;         // sum over tensors of the variances (0 without a measurement)
     double GN;        // sum over tensors of the gradient norms^2
     double C2;        // controller state after the step
     int64_t nC2;
+    int32_t n;        // steps of the launch
+    int32_t pad_;
 };
 constexpr size_t kSlotHdrBytes = 64;
 static_assert(sizeof(SlotHdr) <= kSlotHdrBytes, "slot header");
 
 struct ReduceParams {
-    const double *tile_partials;  // [2 n_tiles]
+    const double *tile_partials;  // [n_slots][2 n_tiles] (tile_stride apart)
     const Chunk *chunks;          // [n_chunks], in tensor order
     const int32_t *chunk_begin;   // [T + 1]: chunks of tensor tau
-    double *chunk_partials;       // [2 n_chunks]
-    double *acc;                  // [2T] device scratch: per-tensor sums
+    double *chunk_partials;       // [n_slots][2 n_chunks] (chunk_stride apart)
+    double *acc;                  // [n_slots][2T] device scratch: per-tensor sums
+    double *sums;                 // [n_slots][2] device scratch: S, the norm total
+    int64_t tile_stride, chunk_stride;   // doubles
     const int32_t *large;         // [n_large] tensors of more than kSmallTensorChunks chunks
     int32_t n_chunks, T, K, n_large;
     int32_t chunks_are_tiles;     // 1: chunk_partials is tile_partials (one tile per chunk)
@@ -177,21 +183,25 @@ struct ReduceParams {
     // large tensor), reduced by one block each; the finishing block then sums
     // the window partials.  n_windows = 0: one block does everything.
     const int32_t *win_begin;     // [n_windows + 1]: first tensor of each window
-    double *win_partials;         // [2 n_windows]: per window, sum of variances, of gradient norms^2
+    double *win_partials;         // [n_slots][2 n_windows]: per window, sum of variances, of gradient norms^2
     int32_t n_windows;
-    int32_t pad2_;
-    double *out;                  // [2T]: variance per tensor, then gradient norm^2 (may be mapped host memory)
-    SlotHdr *hdr;                 // (may be mapped host memory)
-    SchedState *sched;            // non-null: the step's sync is decided and controlled here
+    int32_t n_slots;              // measurements of the launch at most, one record each
+    // Records (header, then the variances and gradient norms^2 per tensor) in
+    // host memory: slots slot0, slot0 + 1, ... of a ring, slot_bytes apart.
+    char *recs;
+    int64_t slot_bytes;
+    int32_t slot0, ring;
+    SchedState *sched;            // the controller state (when.device or control)
+    int32_t control;              // 1: decisions are taken here and the state is kept up
+    SchedState st0;               // control = 0: the state for the records (no sync moves it)
     SchedRule rule;
-    int64_t t;                    // the step
-    double gamma;                 // its rate in fp64 (Algorithm 2's gamma_t)
-    int32_t traced;               // reduce even when no sync is due
+    SpanWhen when;                // as in the launch that is reduced
+    double gamma[kSpanSteps];     // rates in fp64 (Algorithm 2's gamma_t) from step when.t on
 };
 
 // Segmented fixed-order sums of the tile partials (chunks, then tensors, then
-// over tensors) and, with a schedule, Algorithm 2's period decision on the
-// result.
+// over tensors) of every measurement of a launch and, with control, Algorithm
+// 2's period decisions on the results, in step order.
 // Windows of tensors (ReduceParams::win_begin) are cut by the host:
 int32_t reduce_windows(int32_t T, const int32_t *chunk_begin, std::vector<int32_t> *win_begin);
 hipError_t launch_reduce(const ReduceParams &r, hipStream_t st);

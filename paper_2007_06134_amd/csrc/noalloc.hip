@@ -218,7 +218,7 @@ extern "C" int adpsgd_average_noalloc(int32_t K, int64_t P, int64_t row_stride, 
         // between 256 MB and 1 GiB cached accesses measured as fast or faster
         // (18% at K = 32, P = 1.2M), at 8.8 GB 4% slower
         const bool nt = (double)K * (double)P * 8.0 > 1024.0 * 1024 * 1024;
-        if ((e = launch_tile_sync(sp, n_tiles, kAverage, false, vec, nt, 0, st)) != hipSuccess)
+        if ((e = launch_average(sp, n_tiles, false, vec, nt, 0, st)) != hipSuccess)
             return hip_err(e, "sync launch");
     }
     k_tensor_var<<<(unsigned)T, kThreads, 0, st>>>(d_first, d_part, K, d_var);

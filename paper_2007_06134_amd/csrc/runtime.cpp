@@ -67,14 +67,17 @@ namespace {
 
 constexpr int kRing = 32;          // record slots: launches with a reduction in flight at once
 constexpr int kTimedMax = 4096;    // pending timed launches before a harvest
-constexpr int64_t kMaxInflight = 1024;  // launched steps the host has not yet accounted for
-// The driver waits for an outstanding decision when at least this many steps
-// are queued behind it (the GPU stays busy meanwhile); otherwise it lets the
-// device decide, for at most kMaxUncertain steps in a row.
-constexpr int64_t kQueueToWait = 1;
-constexpr int kMaxUncertain = 2;
+// Measurements (syncs, or steps of a traced run) of one launch at most, and the
+// device memory their partial sums may take (one measurement's always fits).
+constexpr int32_t kSpanSlots = 16;
+constexpr int64_t kSpanSlotBytes = int64_t(64) << 20;
+constexpr int64_t kMaxInflight = 64;   // launches the host has not yet accounted for
+// Launches in flight whose end only the device knows, at most: with one queued
+// behind the one that runs, the GPU does not wait for the host to read a record;
+// more keep it busy where a launch is shorter than that takes.
+constexpr int kMaxOpen = 3;
 // Between waits, the driver polls for finished records every kPollEvery launches
-// (each poll is a runtime call; plain steps need no accounting to proceed).
+// (each poll is a runtime call; steps without a record need no accounting to proceed).
 constexpr int64_t kPollEvery = 8;
 // adpsgd_init times the local step's block sizes when one step moves at least
 // this many elements (below it a launch is too short to time reliably).
@@ -89,9 +92,9 @@ constexpr int64_t kMaxK = 65536;
 constexpr int64_t kMaxCounter = int64_t(1) << 32;  // Philox counter words are 32-bit
 
 enum TimedKind { tStep = 0, tFused = 1, tAverage = 2, tSegsum = 3, tTrace = 4, tKinds = 5 };
-// Sampling classes of the timer: the timed kinds, plus the device-decided
-// step kernels whose kind is known only when their record is read.
-enum { cDeviceStep = tKinds, kTimedClasses = tKinds + 1 };
+// Sampling classes of the timer: the timed kinds, plus the spans, whose steps are
+// told apart when they are accounted for.
+enum { cSpan = tKinds, kTimedClasses = tKinds + 1 };
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -121,6 +124,7 @@ struct Plan {
     int64_t n_aligned = 0;  // aligned chunks of kTileElems elements (a sync-tile block each)
     int32_t chunk_tiles = kChunkTiles;
     int32_t n_windows = 0;  // windows of tensors for k_reduce_windows (0: none)
+    int32_t n_slots = 1;    // measurements whose partial sums the workspace holds
 };
 
 Plan count_plan(int32_t T, const int64_t *off) {
@@ -136,6 +140,8 @@ Plan count_plan(int32_t T, const int64_t *off) {
     }
     std::vector<int32_t> win_begin;
     pl.n_windows = reduce_windows(T, chunk_begin.data(), &win_begin);
+    const int64_t per_slot = 16 * (pl.n_tiles + pl.n_chunks + T + pl.n_windows);
+    pl.n_slots = (int32_t)std::min<int64_t>(kSpanSlots, std::max<int64_t>(1, kSpanSlotBytes / per_slot));
     return pl;
 }
 
@@ -160,8 +166,8 @@ void build_plan(int32_t T, const int64_t *off, int32_t chunk_tiles, std::vector<
 }
 
 struct Layout {
-    size_t tiles, chunks, chunk_begin, large, tile_partials, chunk_partials, acc, win_begin, win_partials, sched,
-        chunk_seg, total;
+    size_t tiles, chunks, chunk_begin, large, tile_partials, chunk_partials, acc, win_begin, win_partials, sums,
+        sched, chunk_seg, total;
 };
 
 // A record slot (pinned host memory the reduction writes directly): the
@@ -170,17 +176,19 @@ size_t slot_bytes_for(int32_t T) { return align_up(kSlotHdrBytes + 2 * sizeof(do
 
 Layout layout_for(const Plan &pl, int32_t T) {
     auto at_least_one = [](int64_t n) { return (size_t)std::max<int64_t>(n, 1); };
+    const size_t slots = (size_t)pl.n_slots;
     Layout l;
     l.tiles = 0;
     l.chunks = align_up(l.tiles + sizeof(Tile) * at_least_one(pl.n_tiles), 256);
     l.chunk_begin = align_up(l.chunks + sizeof(Chunk) * at_least_one(pl.n_chunks), 256);
     l.large = align_up(l.chunk_begin + sizeof(int32_t) * (size_t)(T + 1), 256);
     l.tile_partials = align_up(l.large + sizeof(int32_t) * (size_t)T, 256);
-    l.chunk_partials = align_up(l.tile_partials + 2 * sizeof(double) * at_least_one(pl.n_tiles), 256);
-    l.acc = align_up(l.chunk_partials + 2 * sizeof(double) * at_least_one(pl.n_chunks), 256);
-    l.win_begin = align_up(l.acc + 2 * sizeof(double) * (size_t)T, 256);
+    l.chunk_partials = align_up(l.tile_partials + slots * 2 * sizeof(double) * at_least_one(pl.n_tiles), 256);
+    l.acc = align_up(l.chunk_partials + slots * 2 * sizeof(double) * at_least_one(pl.n_chunks), 256);
+    l.win_begin = align_up(l.acc + slots * 2 * sizeof(double) * (size_t)T, 256);
     l.win_partials = align_up(l.win_begin + sizeof(int32_t) * (size_t)(pl.n_windows + 1), 256);
-    l.sched = align_up(l.win_partials + 2 * sizeof(double) * at_least_one(pl.n_windows), 256);
+    l.sums = align_up(l.win_partials + slots * 2 * sizeof(double) * at_least_one(pl.n_windows), 256);
+    l.sched = align_up(l.sums + slots * 2 * sizeof(double), 256);
     l.chunk_seg = align_up(l.sched + sizeof(SchedState), 256);
     l.total = align_up(l.chunk_seg + sizeof(int32_t) * (size_t)(pl.n_aligned + 1), 256);
     return l;
@@ -199,9 +207,10 @@ int hip_fail(hipError_t e, const char *what) {
     } while (0)
 
 struct TimedLaunch {
-    int kind;
+    int kind;        // -1: a span that is not accounted for
     hipEvent_t start, stop;
     int32_t steps;   // launches of one step that this one stands for
+    int32_t syncs;   // of them, those with a sync (a span's; the others are of `kind`)
 };
 
 }  // namespace
@@ -235,7 +244,9 @@ struct adpsgd_ctx {
     bool chunks_are_tiles = false;  // every tile is its own chunk (small problems)
     double *d_tile_partials = nullptr;
     double *d_chunk_partials = nullptr;
-    double *d_acc = nullptr;        // [2T] reduction scratch
+    double *d_acc = nullptr;        // [n_slots][2T] reduction scratch
+    double *d_sums = nullptr;       // [n_slots][2]
+    int32_t n_slots = 1;            // measurements of one launch at most
     SchedState *d_sched = nullptr;  // the controller state as the device sees it during a run
     char *h_slots = nullptr;        // [kRing] record slots: pinned, coherent host memory
     char *d_slots = nullptr;        // the same slots as the device addresses them
@@ -245,8 +256,7 @@ struct adpsgd_ctx {
     adpsgd_state st{};
     bool vec = true;                // row stride % 4 == 0: rows 16-byte aligned, dwordx4 groups
     bool nontemporal = false;       // stream x and m past the caches (large working sets)
-    // the sync-tile kernel's choice of the same, timed at init on large working
-    // sets: the step + sync modes (fused, device-decided, traced) and the separate sync
+    // the same for spans and for the separate sync, timed at init on large working sets
     bool sync_nt = false;
     bool average_nt = false;
     int32_t policy = ADPSGD_LAUNCH_HYBRID;
@@ -312,8 +322,8 @@ int pool_event(adpsgd_ctx *c, hipEvent_t *ev) {
 }
 
 // Fold finished timed launches into the totals (all of them if wait_all).  A
-// launch whose kind is still open (-1: a device-decided step the driver has
-// not accounted for) stops a non-waiting harvest.
+// launch whose kind is still open (-1: a span the driver has not accounted
+// for) stops a non-waiting harvest.  A span's time is shared evenly by its steps.
 int harvest(adpsgd_ctx *c, bool wait_all) {
     while (!c->timed.empty()) {
         TimedLaunch tl = c->timed.front();
@@ -328,8 +338,11 @@ int harvest(adpsgd_ctx *c, bool wait_all) {
         float ms = 0.f;
         HIP_TRY(hipEventElapsedTime(&ms, tl.start, tl.stop));
         const int kind = tl.kind < 0 ? tStep : tl.kind;
-        c->t_ms[kind] += ms;
-        c->t_n[kind] += tl.steps;
+        const double each = (double)ms / std::max(tl.steps, 1);
+        c->t_ms[kind] += each * (tl.steps - tl.syncs);
+        c->t_n[kind] += tl.steps - tl.syncs;
+        c->t_ms[tFused] += each * tl.syncs;
+        c->t_n[tFused] += tl.syncs;
         c->ev_pool.push_back(tl.start);
         c->ev_pool.push_back(tl.stop);
         c->timed.pop_front();
@@ -341,12 +354,12 @@ int harvest(adpsgd_ctx *c, bool wait_all) {
 // Launch, with HIP events around it when timing is on and this launch is
 // sampled: a launch of `steps` steps counts as that many of its class, and is
 // timed when no more than one in timing_every of the class (rounded up) is
-// timed with it.  kind -1: decided later (set_timed_kind).  *seq (may be null)
-// receives the launch's sequence number, or -1 when it is not timed.
+// timed with it.  kind -1: a span, described later (set_timed_span).  *seq (may
+// be null) receives the launch's sequence number, or -1 when it is not timed.
 template <class F>
 int timed_launch(adpsgd_ctx *c, int kind, F launch, int64_t *seq = nullptr, int32_t steps = 1) {
     if (seq) *seq = -1;
-    const int cls = kind < 0 ? cDeviceStep : kind;
+    const int cls = kind < 0 ? cSpan : kind;
     bool sampled = false;
     if (c->timing) {
         c->class_seen[cls] += steps;
@@ -365,7 +378,7 @@ int timed_launch(adpsgd_ctx *c, int kind, F launch, int64_t *seq = nullptr, int3
             if (rc) return rc;
         }
     }
-    TimedLaunch tl{kind, nullptr, nullptr, steps};
+    TimedLaunch tl{kind, nullptr, nullptr, steps, 0};
     int rc = pool_event(c, &tl.start);
     if (rc) return rc;
     rc = pool_event(c, &tl.stop);
@@ -378,9 +391,17 @@ int timed_launch(adpsgd_ctx *c, int kind, F launch, int64_t *seq = nullptr, int3
     return ok();
 }
 
-void set_timed_kind(adpsgd_ctx *c, int64_t seq, int kind) {
+// Span seq took n steps, `syncs` of them with a sync and the others of `kind`.
+void set_timed_span(adpsgd_ctx *c, int64_t seq, int kind, int32_t n, int32_t syncs) {
     const int64_t i = seq - c->timed_popped;
-    if (seq >= 0 && i >= 0 && i < (int64_t)c->timed.size()) c->timed[(size_t)i].kind = kind;
+    if (seq < 0 || i < 0 || i >= (int64_t)c->timed.size()) return;
+    TimedLaunch &tl = c->timed[(size_t)i];
+    // (the sampling counted the most steps the span could take)
+    c->class_seen[cSpan] += n - tl.steps;
+    c->class_timed[cSpan] += n - tl.steps;
+    tl.kind = kind;
+    tl.steps = n;
+    tl.syncs = syncs;
 }
 
 StepParams step_params(const adpsgd_ctx *c, int64_t t, int32_t n = 1) {
@@ -417,32 +438,64 @@ int enqueue_steps(adpsgd_ctx *c, int64_t t0, int64_t n) {
     return ok();
 }
 
-SyncParams sync_params(const adpsgd_ctx *c, int64_t t) {
+SyncParams sync_params(const adpsgd_ctx *c) {
     SyncParams sp;
-    sp.s = step_params(c, t);
+    sp.s = step_params(c, 0);
     sp.tiles = c->d_tiles;
     sp.partials = c->d_tile_partials;
     sp.chunk_seg = c->d_chunk_seg;
     sp.n_chunks = (int64_t)c->chunk_seg.size() - 1;
-    sp.sched = c->d_sched;
-    sp.rule = rule_of(&c->hp);
     return sp;
 }
 
-char *slot_dev(const adpsgd_ctx *c, int slot) { return c->d_slots + (size_t)slot * c->slot_bytes; }
+// A span the host planned: steps t .. t + n - 1, bit j of syncs set when a sync
+// follows step t + j; measure: every step is measured.
+SpanWhen planned(int64_t t, int32_t n, uint64_t syncs, bool measure) {
+    return SpanWhen{t, t + n, syncs, n, 0, 1, measure ? 1 : 0};
+}
+int measurements(const SpanWhen &w) {
+    if (w.measure) return w.n;
+    return w.device ? 1 : __builtin_popcountll(w.syncs);
+}
+
+// Rates from step w.t on: a launch with an unknown first step may begin up to
+// kSpanSteps - 1 steps later.
+int32_t n_rates(const SpanWhen &w) { return w.device && !w.known ? kSpanSteps : w.n; }
+
+SpanParams span_params(const adpsgd_ctx *c, const SpanWhen &w) {
+    SpanParams sp;
+    static_cast<SyncParams &>(sp) = sync_params(c);
+    sp.s = step_params(c, w.t, n_rates(w));
+    sp.slot_stride = 2 * (int64_t)c->tiles.size();
+    sp.sched = c->d_sched;
+    sp.rule = rule_of(&c->hp);
+    sp.when = w;
+    sp.avg_m = c->hp.avg_momentum;
+    sp.pad_ = 0;
+    return sp;
+}
+
+hipError_t launch_span_of(const adpsgd_ctx *c, const SpanWhen &w, bool nt, hipStream_t st) {
+    return launch_span(span_params(c, w), (int64_t)c->tiles.size(), c->vec, nt, c->nontemporal, c->step_shape, st);
+}
+
 const char *slot_host(const adpsgd_ctx *c, int slot) { return c->h_slots + (size_t)slot * c->slot_bytes; }
 
-// The reduction after a sync-tile kernel at step t, writing its record to the
-// slot at device address `slot` (with the controller on the device when ctl).
-ReduceParams reduce_params(const adpsgd_ctx *c, int mode, int64_t t, char *slot, bool ctl) {
+// The reduction of a launch's measurements, their records written from slot
+// `slot0` on of the ring at device address recs (with the controller on the
+// device when control).
+ReduceParams reduce_params(const adpsgd_ctx *c, const SpanWhen &w, char *recs, int slot0, int ring, bool control) {
     ReduceParams r;
     r.tile_partials = c->d_tile_partials;
     r.chunks = c->d_chunks;
     r.chunk_begin = c->d_chunk_begin;
     r.chunk_partials = c->chunks_are_tiles ? c->d_tile_partials : c->d_chunk_partials;
+    r.tile_stride = 2 * (int64_t)c->tiles.size();
+    r.chunk_stride = 2 * (int64_t)c->chunks.size();
     r.chunks_are_tiles = c->chunks_are_tiles ? 1 : 0;
     r.block0 = 0;
     r.acc = c->d_acc;
+    r.sums = c->d_sums;
     r.n_chunks = (int32_t)c->chunks.size();
     r.T = c->T;
     r.K = c->K;
@@ -451,48 +504,96 @@ ReduceParams reduce_params(const adpsgd_ctx *c, int mode, int64_t t, char *slot,
     r.win_begin = c->d_win_begin;
     r.win_partials = c->d_win_partials;
     r.n_windows = c->win_begin.empty() ? 0 : (int32_t)c->win_begin.size() - 1;
-    r.pad2_ = 0;
-    r.hdr = reinterpret_cast<SlotHdr *>(slot);
-    r.out = reinterpret_cast<double *>(slot + kSlotHdrBytes);
-    r.sched = ctl ? c->d_sched : nullptr;
+    r.n_slots = measurements(w);
+    r.recs = recs;
+    r.slot_bytes = (int64_t)c->slot_bytes;
+    r.slot0 = slot0;
+    r.ring = ring;
+    r.sched = c->d_sched;
+    r.control = control ? 1 : 0;
+    r.st0 = SchedState{c->st.t, c->st.cnt, c->st.nC2, c->st.C2, c->st.p, 0};
     r.rule = rule_of(&c->hp);
-    r.t = t;
-    r.gamma = adpsgd_lr(&c->hp, t);
-    r.traced = mode == kDeviceTrace ? 1 : 0;
+    r.when = w;
+    for (int32_t j = 0; j < n_rates(w); ++j) r.gamma[j] = adpsgd_lr(&c->hp, w.t + j);
     return r;
 }
 
-// The sync-tile kernel of the given mode at step t, then the reduction into
-// record slot `slot` (with the controller on the device when ctl), then the
-// slot's event.  *step_seq: the timed sequence number of the tile kernel (its
-// kind is open for the device-decided modes).
-int enqueue_sync(adpsgd_ctx *c, int mode, int64_t t, int slot, bool ctl, int64_t *step_seq) {
-    const bool dev = mode == kDevice || mode == kDeviceTrace;
-    const SyncParams sp = sync_params(c, t);
-    const int64_t n_tiles = (int64_t)c->tiles.size();
-    const int kind = dev ? -1 : mode == kAverage ? tAverage : tFused;
-    int rc = timed_launch(
-        c, kind,
-        [&] {
-            return launch_tile_sync(sp, n_tiles, mode, c->hp.avg_momentum != 0, c->vec,
-                                    mode == kAverage ? c->average_nt : c->sync_nt,
-                                    mode == kAverage ? c->average_cap : 0, c->stream);
-        },
-        step_seq);
+// Sync now, without a step (average) or after step t: the kernel, then the
+// reduction into record slot 0, then that slot's event.
+int enqueue_sync(adpsgd_ctx *c, bool average, int64_t t) {
+    const SpanWhen w = planned(t, 1, 1, false);
+    int rc = timed_launch(c, average ? tAverage : tFused, [&] {
+        return average ? launch_average(sync_params(c), (int64_t)c->tiles.size(), c->hp.avg_momentum != 0, c->vec,
+                                        c->average_nt, c->average_cap, c->stream)
+                       : launch_span_of(c, w, c->sync_nt, c->stream);
+    });
     if (rc) return rc;
-    const ReduceParams r = reduce_params(c, mode, t, slot_dev(c, slot), ctl);
+    const ReduceParams r = reduce_params(c, w, c->d_slots, 0, kRing, false);
     rc = timed_launch(c, tSegsum, [&] { return launch_reduce(r, c->stream); });
     if (rc) return rc;
-    HIP_TRY(hipEventRecord(c->ring_ev[slot], c->stream));
+    HIP_TRY(hipEventRecord(c->ring_ev[0], c->stream));
     return ok();
 }
 
-// Capture steps t0 .. t0 + due.size() - 1 as a graph, launched as the eager
-// driver launches a schedule it knows in advance: plain steps, and for the
-// j-th sync the fused step + sync and the reduction (controller on the device)
-// into the j-th graph record slot.  No events: records are read after the
-// whole graph has run.
-int capture_run(adpsgd_ctx *c, int64_t t0, const std::vector<char> &due, int64_t n_sync) {
+// A span, then the reduction of its measurements into the record slots from
+// `slot0` on, then the event of the last of them.  *seq: the timed sequence
+// number of the span.
+int enqueue_span(adpsgd_ctx *c, const SpanWhen &w, int slot0, bool control, int64_t *seq) {
+    int rc = timed_launch(c, -1, [&] { return launch_span_of(c, w, c->sync_nt, c->stream); }, seq, w.n);
+    if (rc) return rc;
+    const ReduceParams r = reduce_params(c, w, c->d_slots, slot0, kRing, control);
+    rc = timed_launch(c, tSegsum, [&] { return launch_reduce(r, c->stream); }, nullptr, r.n_slots);
+    if (rc) return rc;
+    HIP_TRY(hipEventRecord(c->ring_ev[(slot0 + r.n_slots - 1) % kRing], c->stream));
+    return ok();
+}
+
+// Step st->t of a known schedule: true if a sync follows it (the counter then
+// restarts; p stays, whatever the sync decides).
+bool plan_step(const SchedRule &rule, adpsgd_state *st) {
+    const int64_t t = st->t++;
+    st->cnt += 1;
+    st->p = period_at(rule, st->p, t);
+    const bool due = sync_due(rule, st->cnt, st->p, t);
+    if (due) st->cnt = 0;
+    return due;
+}
+
+// The next launch of a schedule known from state st on: steps up to `most` and
+// `end`, ending after the last sync that fits n_slots (every step needs a slot
+// when all are measured), after a sync whose outcome may move p, or at the end.
+// Without measurements it is plain steps.  st is moved to the state after it.
+SpanWhen plan_span(const adpsgd_ctx *c, adpsgd_state *st, int64_t end, bool measure) {
+    const SchedRule rule = rule_of(&c->hp);
+    SpanWhen w = planned(st->t, 0, 0, measure);
+    int slots = 0;
+    adpsgd_state after_sync = *st;   // the state after the last sync of the span
+    int32_t n_sync = 0;
+    while (w.n < kSpanSteps && st->t < end && slots < c->n_slots) {
+        const int64_t t = st->t;
+        const bool due = plan_step(rule, st);
+        if (due) w.syncs |= uint64_t(1) << w.n;
+        ++w.n;
+        if (due || measure) ++slots;
+        if (due) {
+            after_sync = *st;
+            n_sync = w.n;
+        }
+        if (due && sync_decisive(rule, t)) break;
+    }
+    // the steps after the last sync go with the next launch, which measures them
+    // too, unless the run ends here
+    if (n_sync > 0 && st->t < end && !measure) {
+        *st = after_sync;
+        w.n = n_sync;
+    }
+    w.end = w.t + w.n;
+    return w;
+}
+
+// Capture the spans of a schedule that no decision moves as a graph: the spans, and after each the reduction into as many of the graph's record slots.
+// No events: records are read after the whole graph has run.
+int capture_run(adpsgd_ctx *c, const std::vector<SpanWhen> &spans, int64_t n_sync) {
     drop_graph(c);
     if (n_sync > c->gslot_cap) {
         if (c->h_gslots) (void)hipHostFree(c->h_gslots);
@@ -505,23 +606,20 @@ int capture_run(adpsgd_ctx *c, int64_t t0, const std::vector<char> &due, int64_t
     }
     if (!c->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
     const hipStream_t cs = c->cap_stream;
-    const int64_t n_tiles = (int64_t)c->tiles.size();
     HIP_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
     hipError_t e = hipSuccess;
-    int64_t j = 0;
-    for (size_t i = 0; i < due.size() && e == hipSuccess; ++i) {
-        const int64_t t = t0 + (int64_t)i;
-        if (!due[i]) {
-            int32_t m = 1;
-            while (m < kSpanSteps && i + 1 < due.size() && !due[i + 1]) ++i, ++m;
-            e = launch_local_step(step_params(c, t, m), c->vec, c->nontemporal, c->step_shape, cs);
+    int slot = 0;
+    for (const SpanWhen &w : spans) {
+        const int m = measurements(w);
+        if (m == 0) {
+            e = launch_local_step(step_params(c, w.t, w.n), c->vec, c->nontemporal, c->step_shape, cs);
         } else {
-            e = launch_tile_sync(sync_params(c, t), n_tiles, kFused, c->hp.avg_momentum != 0, c->vec, c->sync_nt, 0,
-                                 cs);
+            e = launch_span_of(c, w, c->sync_nt, cs);
             if (e == hipSuccess)
-                e = launch_reduce(reduce_params(c, kFused, t, c->d_gslots + (size_t)j * c->slot_bytes, true), cs);
-            ++j;
+                e = launch_reduce(reduce_params(c, w, c->d_gslots, slot, (int)std::max<int64_t>(n_sync, 1), false), cs);
         }
+        slot += m;
+        if (e != hipSuccess) break;
     }
     hipGraph_t g = nullptr;
     const hipError_t e_end = hipStreamEndCapture(cs, &g);
@@ -667,35 +765,21 @@ hipError_t fastest_in_blocks(adpsgd_ctx *c, int n, int reps, Launch launch, int 
     return e;
 }
 
-// Whether the step + sync modes keep non-temporal accesses.  Beyond 1 GiB of
-// x and m they do (measured 10% faster at K = 8, P = 138M).  Between the
-// last-level cache's 256 MB and 1 GiB it depends on the problem (the fused
-// step + sync measured 14% faster without them at K = 32, P = 1.2M, and 14%
-// slower at K = 8, P = 11.2M), so time periods of four steps (three plain
-// steps, non-temporal as always, then the fused step + sync) with the sync's
-// accesses non-temporal and not.  The launches step x and m, which the caller
-// zeroes afterwards.
+// Whether spans keep non-temporal accesses.  Beyond 1 GiB of x and m they do
+// (measured 6% faster at K = 8, P = 138M).  Between the last-level cache's 256 MB
+// and 1 GiB it depends on the problem (four steps with a sync measured 17% faster
+// without them at K = 32, P = 1.2M, and 14% slower at K = 8, P = 11.2M), so time
+// such spans both ways.  The launches step x and m, which the caller zeroes
+// afterwards.
 constexpr double kSyncNtTuneMaxBytes = 1024.0 * 1024 * 1024;
 
 hipError_t tune_sync_nt(adpsgd_ctx *c) {
     c->sync_nt = c->nontemporal;
     if (!c->nontemporal || c->tiles.empty() || (double)c->K * (double)c->P * 8.0 > kSyncNtTuneMaxBytes)
         return hipSuccess;
-    const StepParams stp = step_params(c, 0);
-    const SyncParams sp = sync_params(c, 3);
-    const int64_t n_tiles = (int64_t)c->tiles.size();
     int win = 0;
     const hipError_t e = fastest_in_blocks(
-        c, 2, 3,
-        [&](int j) {
-            hipError_t le = hipSuccess;
-            for (int i = 0; i < 3 && le == hipSuccess; ++i)
-                le = launch_local_step(stp, c->vec, c->nontemporal, c->step_shape, c->stream);
-            if (le == hipSuccess)
-                le = launch_tile_sync(sp, n_tiles, kFused, c->hp.avg_momentum != 0, c->vec, j == 0, 0, c->stream);
-            return le;
-        },
-        &win);
+        c, 2, 6, [&](int j) { return launch_span_of(c, planned(0, 4, 8, false), j == 0, c->stream); }, &win);
     if (e == hipSuccess) c->sync_nt = win == 0;
     return e;
 }
@@ -706,19 +790,19 @@ hipError_t tune_sync_nt(adpsgd_ctx *c) {
 // tune_sync_nt), with and without non-temporal accesses, on the context's own
 // buffers (zeroed again afterwards).
 hipError_t tune_average(adpsgd_ctx *c) {
-    const int waves = sync_tile_waves(c->K, kAverage);
+    const int waves = average_tile_waves(c->K);
     if (waves <= 0 || c->tiles.empty()) return hipSuccess;
     const int caps[2] = {0, std::max(1, kAverageCapWaves / waves)};
     const bool both = c->nontemporal && (double)c->K * (double)c->P * 8.0 <= kSyncNtTuneMaxBytes;
     const int n = both ? 4 : 2;   // j: cap caps[j & 1], non-temporal while j < 2 (if at all)
-    const SyncParams sp = sync_params(c, 0);
+    const SyncParams sp = sync_params(c);
     const int64_t n_tiles = (int64_t)c->tiles.size();
     int win = 0;
     const hipError_t e = fastest_in_blocks(
         c, n, 3,
         [&](int j) {
-            return launch_tile_sync(sp, n_tiles, kAverage, c->hp.avg_momentum != 0, c->vec, c->nontemporal && j < 2,
-                                    caps[j & 1], c->stream);
+            return launch_average(sp, n_tiles, c->hp.avg_momentum != 0, c->vec, c->nontemporal && j < 2, caps[j & 1],
+                                  c->stream);
         },
         &win);
     if (e == hipSuccess) {
@@ -800,6 +884,8 @@ extern "C" int adpsgd_init(int32_t K, int64_t P, const int64_t *offsets, int32_t
     c->d_tile_partials = (double *)(ws + lay.tile_partials);
     c->d_chunk_partials = (double *)(ws + lay.chunk_partials);
     c->d_acc = (double *)(ws + lay.acc);
+    c->d_sums = (double *)(ws + lay.sums);
+    c->n_slots = plan.n_slots;
     c->d_sched = (SchedState *)(ws + lay.sched);
     c->d_chunk_seg = (int32_t *)(ws + lay.chunk_seg);
     if (!chunk_segments(c->tiles, plan.n_aligned, &c->chunk_seg)) {
@@ -900,7 +986,7 @@ static int sync_now(adpsgd_ctx *c, bool fused, double *var_out) {
     DeviceScope dev_(c);
     if (!var_out) return fail(ADPSGD_EINVAL, "var_out is NULL");
     if (fused && c->st.t + 1 > kMaxCounter) return fail(ADPSGD_EINVAL, "step index would reach 2^32");
-    if (int rc = enqueue_sync(c, fused ? kFused : kAverage, c->st.t, 0, false, nullptr)) return rc;
+    if (int rc = enqueue_sync(c, !fused, c->st.t)) return rc;
     HIP_TRY(hipEventSynchronize(c->ring_ev[0]));
     std::memcpy(var_out, slot_host(c, 0) + kSlotHdrBytes, sizeof(double) * c->T);
     if (fused) {
@@ -926,18 +1012,17 @@ extern "C" int adpsgd_schedule(adpsgd_ctx *c, const double *var, int32_t *next_p
 
 // Algorithm 2 for n_steps steps (adpsgd_run, adpsgd_run_traced).
 //
-// The host plans each step from its replay of the schedule: a step that ends
-// no period whatever the decisions still in flight runs the plain local step;
-// any other step runs the sync-tile kernel in a device-decided mode, which
-// steps and, iff Algorithm 2's counter (read from the device copy of the
-// controller state) says so, averages, followed by the reduction kernel that
-// sums the variances and takes Algorithm 2's period decision on the device.  After a decisive
-// sync the host waits for its outcome only while the GPU has queued steps
-// behind it; otherwise the device decides the next steps itself, so the GPU
-// never idles on a host round trip.  Every record is read back in order,
-// replayed by the host controller (same rules, same fp64 operations) and
-// checked against the device's decision.  A traced run sends every step
-// through the reduction.
+// The host plans launches from its replay of the schedule.  While that is exact
+// a launch takes as many steps and syncs as it can (plan_span), up to and with
+// the first sync whose outcome may move p.  What follows such a sync is a span
+// that the device ends: it takes steps until Algorithm 2's counter (read from the
+// device copy of the controller state) says that a sync is due, so neither its
+// length nor, for the launch after it, its first step need be known to the host.
+// The reduction behind every span sums the variances and takes Algorithm 2's
+// decisions on the device, so the GPU never waits for a host round trip.  Every
+// record is read back in order, replayed by the host controller (same rules,
+// same fp64 operations) and checked against the device's decision.  A traced run
+// measures every step of its launches.
 static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_t log_cap, double *var_log,
                     adpsgd_step_rec *trace, int64_t trace_cap, int64_t *n_syncs) {
     Range range_("adpsgd_run");
@@ -951,129 +1036,101 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
     const adpsgd_hparams &hp = c->hp;
     const SchedRule rule = rule_of(&hp);
     const bool traced = trace != nullptr;
+    const bool adaptive = hp.period_mode == ADPSGD_PERIOD_ADAPTIVE;
+    const bool by_step = c->policy == ADPSGD_LAUNCH_DEVICE;   // every step decided on the device
+    const bool control = adaptive || by_step;   // the controller state lives on the device
     const int64_t t0 = c->st.t, end = t0 + n_steps;
-
-    // The schedule from the host's point of view: exact, or the period known
-    // to lie in [lo, hi] (decisions in flight move p by at most one each), or
-    // unknown once a step whose sync the host could not predict is in flight.
-    struct Plan { bool exact; int64_t cnt; int32_t lo, hi; };
-    enum Cls { cPlain, cDue, cUncertain };
-    auto advance = [&](Plan &pl, int64_t t) -> Cls {
-        if (!pl.exact) return cUncertain;
-        pl.cnt += 1;
-        pl.lo = period_at(rule, pl.lo, t);
-        pl.hi = period_at(rule, pl.hi, t);
-        const bool due_lo = sync_due(rule, pl.cnt, pl.lo, t), due_hi = sync_due(rule, pl.cnt, pl.hi, t);
-        if (due_lo != due_hi) { pl.exact = false; return cUncertain; }
-        if (!due_lo) return cPlain;
-        pl.cnt = 0;
-        if (sync_decisive(rule, t)) {
-            pl.lo = std::max(pl.lo - 1, 1);
-            pl.hi = pl.hi < rule.p_max ? pl.hi + 1 : rule.p_max;
-        }
-        return cDue;
-    };
 
     // A run whose schedule is fixed in advance (constant-period modes) on a
     // small, launch-bound problem replays a captured graph of the whole run.
     const bool graph_mode = c->policy == ADPSGD_LAUNCH_HYBRID && !traced && !c->timing && n_steps > 0 &&
-                            n_steps <= kGraphMaxSteps && hp.period_mode != ADPSGD_PERIOD_ADAPTIVE &&
-                            (double)c->K * (double)c->P < kGraphMaxElems;
-    auto slot_rec = [&](int slot) -> const char * {
-        return graph_mode ? c->h_gslots + (size_t)slot * c->slot_bytes : slot_host(c, slot);
-    };
+                            n_steps <= kGraphMaxSteps && !adaptive && (double)c->K * (double)c->P < kGraphMaxElems;
 
-    struct Entry { int64_t t; bool dev, uncertain; int slot; int64_t seq; int32_t n; };   // n plain steps, or one of the device's
+    // A launch in flight: what it takes, and its record slots (slot0 < 0: none).
+    struct Entry { SpanWhen w; int slot0, n_slots; int64_t seq; };
     std::deque<Entry> inflight;
     adpsgd_state known = c->st;   // the host controller after every accounted step
-    Plan plan{true, known.cnt, known.p, known.p};
-    bool dirty = false;
-    int64_t launched = t0, n_done = 0, n_slots = 0, n_launches = 0;
-    int n_dev = 0, n_uncertain = 0;
+    int64_t n_done = 0, n_launches = 0, next_slot = 0, slots_used = 0;
+    bool dirty = false;           // a record was read: the launches ahead are known better
     int status = ADPSGD_OK;
 
-    // Account for the front entry (finished, or a plain step): replay it on the
-    // host and check the device's record against the replay.
-    auto account = [&](const Entry &e) -> int {
-        int32_t due = 0;
-        for (int32_t j = 0; j < e.n; ++j) {
-            (void)adpsgd_sched_step(&hp, &known, &due);
-            if (!e.dev && due) return fail(ADPSGD_ESTATE, "internal: a plain step ended a period");
-        }
-        if (!e.dev) return ADPSGD_OK;
+    auto slot_rec = [&](int slot) -> const char * {
+        return graph_mode ? c->h_gslots + (size_t)slot * c->slot_bytes : slot_host(c, slot % kRing);
+    };
+    // Account for one measurement: step t, in record slot `slot`.
+    auto account_slot = [&](int slot, int64_t t, bool due) -> int {
         SlotHdr hdr;
-        std::memcpy(&hdr, slot_rec(e.slot), sizeof hdr);
-        const double *var = reinterpret_cast<const double *>(slot_rec(e.slot) + kSlotHdrBytes);
-        if (hdr.t != e.t || hdr.due != due)
-            return fail(ADPSGD_ESTATE, "device and host schedules disagree at step " + std::to_string(e.t));
-        set_timed_kind(c, e.seq, due ? tFused : traced ? tTrace : tStep);
-        const double gamma = adpsgd_lr(&hp, e.t);
-        if (traced && e.t - t0 < trace_cap)
-            trace[e.t - t0] = adpsgd_step_rec{e.t, due, known.p, hdr.S, hdr.GN, gamma};
+        std::memcpy(&hdr, slot_rec(slot), sizeof hdr);
+        const double *var = reinterpret_cast<const double *>(slot_rec(slot) + kSlotHdrBytes);
+        if (hdr.t != t || (hdr.due != 0) != due)
+            return fail(ADPSGD_ESTATE, "device and host schedules disagree at step " + std::to_string(t));
+        const double gamma = adpsgd_lr(&hp, t);
+        if (traced && t - t0 < trace_cap)
+            trace[t - t0] = adpsgd_step_rec{t, due ? 1 : 0, known.p, hdr.S, hdr.GN, gamma};
         if (!due) return ADPSGD_OK;
         const int32_t p_in_force = known.p;
         double margin = std::numeric_limits<double>::quiet_NaN();
-        const int rc = adpsgd_sched_on_sync(&hp, &known, e.t, hdr.S, &margin);
+        const int rc = adpsgd_sched_on_sync(&hp, &known, t, hdr.S, &margin);
         if (n_done < log_cap) {
-            log[n_done] = adpsgd_sync_rec{e.t, p_in_force, 0, hdr.S, known.C2, gamma, margin};
+            log[n_done] = adpsgd_sync_rec{t, p_in_force, 0, hdr.S, known.C2, gamma, margin};
             if (var_log) std::memcpy(var_log + (size_t)n_done * c->T, var, sizeof(double) * c->T);
         }
         ++n_done;
         // (a non-finite S still restarted the counter; only p and C2 stay)
         if (rc) return hdr.status == rc ? rc : fail(ADPSGD_ESTATE, "device and host disagree on a non-finite S");
         if (hdr.status != ADPSGD_OK || hdr.p_next != known.p || hdr.C2 != known.C2 || hdr.nC2 != known.nC2)
-            return fail(ADPSGD_ESTATE, "device and host controllers disagree at step " + std::to_string(e.t));
+            return fail(ADPSGD_ESTATE, "device and host controllers disagree at step " + std::to_string(t));
         return ADPSGD_OK;
     };
-    // Account for every entry at the front that is finished (all of them,
-    // waiting, if wait_front: then at least the front one).
-    auto drain = [&](bool wait_front) -> int {
-        while (!inflight.empty()) {
-            const Entry e = inflight.front();
-            if (e.dev) {
-                hipError_t q;
-                if (wait_front) {
-                    Range wait_("adpsgd_run: wait for a record");
-                    q = hipEventSynchronize(c->ring_ev[e.slot]);
-                } else {
-                    q = hipEventQuery(c->ring_ev[e.slot]);
-                }
-                if (q == hipErrorNotReady) break;
-                if (q != hipSuccess) return hip_fail(q, "wait for a record");
-                wait_front = false;
-                --n_dev;
-                if (e.uncertain) --n_uncertain;
-                dirty = true;
-            }
-            inflight.pop_front();
-            const int rc = account(e);
-            // after a failure the remaining records are still accounted for
-            // (the steps ran); the first error is the one reported
-            if (rc && status == ADPSGD_OK) status = rc;
+    // Account for a finished launch: replay its steps on the host and check the
+    // device's records against the replay.  After a failure the remaining records
+    // are still accounted for (the steps ran); the first error is the one reported.
+    auto account = [&](const Entry &e) -> int {
+        int first = ADPSGD_OK;
+        int32_t n = e.w.n, n_sync = 0;
+        if (e.w.device) {
+            SlotHdr hdr;
+            std::memcpy(&hdr, slot_rec(e.slot0), sizeof hdr);
+            n = hdr.n;
+            if (n < 0 || n > e.w.n || known.t + n > end) return fail(ADPSGD_ESTATE, "internal: a launch's record is not whole");
         }
-        return ADPSGD_OK;
+        int slot = e.slot0;
+        for (int32_t j = 0; j < n; ++j) {
+            const int64_t t = known.t;
+            int32_t due = 0;
+            (void)adpsgd_sched_step(&hp, &known, &due);
+            // a launch that the device ends, ends with its sync and not before
+            // (or at the most steps it was given)
+            const bool planned_due = e.w.device ? j == n - 1 && due : (e.w.syncs >> j) & 1;
+            const bool cut = e.w.device && j == n - 1 && !due && n < e.w.n && known.t < end && e.w.known;
+            if ((due != 0) != planned_due || cut) {
+                if (!first) first = fail(ADPSGD_ESTATE, "device and host schedules disagree at step " + std::to_string(t));
+                if (due) known.cnt = 0;
+                continue;
+            }
+            n_sync += due;
+            if (!due && !e.w.measure) continue;
+            const int rc = account_slot(slot++, t, due != 0);
+            if (rc && !first) first = rc;
+        }
+        set_timed_span(c, e.seq, traced ? tTrace : tStep, n, n_sync);
+        return first;
     };
 
-    if (n_steps > 0) {
-        *c->h_sched = SchedState{known.t, known.cnt, known.nC2, known.C2, known.p, 0};
-        HIP_TRY(hipMemcpyAsync(c->d_sched, c->h_sched, sizeof(SchedState), hipMemcpyHostToDevice, c->stream));
-    }
     if (graph_mode) {
-        // the schedule, from the host controller alone (no decision moves p)
-        std::vector<char> due((size_t)n_steps);
+        // the launches, from the host controller alone (no decision moves p)
+        std::vector<SpanWhen> spans;
         adpsgd_state pl = known;
         int64_t n_sync = 0;
-        for (int64_t j = 0; j < n_steps; ++j) {
-            int32_t d = 0;
-            (void)adpsgd_sched_step(&hp, &pl, &d);
-            due[(size_t)j] = (char)d;
-            if (d) { pl.cnt = 0; ++n_sync; }
+        while (pl.t < end) {
+            spans.push_back(plan_span(c, &pl, end, false));
+            n_sync += measurements(spans.back());
         }
         const int64_t key[7] = {t0, n_steps, known.cnt, known.p, c->step_shape.block, c->step_shape.lds,
                                 c->step_shape.row_chunks};
         if (!c->graph_exec || std::memcmp(key, c->graph_key, sizeof key) != 0) {
             Range cap_("adpsgd_run: capture a graph");
-            if (int rc = capture_run(c, t0, due, n_sync)) return rc;
+            if (int rc = capture_run(c, spans, n_sync)) return rc;
             std::memcpy(c->graph_key, key, sizeof key);
             ++c->graph_captures;
         }
@@ -1084,83 +1141,141 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
             HIP_TRY(hipStreamSynchronize(c->stream));
         }
         int slot = 0;
-        for (int64_t j = 0; j < n_steps; ++j) {
-            const Entry e{t0 + j, due[(size_t)j] != 0, false, due[(size_t)j] ? slot++ : -1, -1, 1};
-            const int rc = account(e);
+        for (const SpanWhen &w : spans) {
+            const int rc = account(Entry{w, slot, measurements(w), -1});
             if (rc && status == ADPSGD_OK) status = rc;
+            slot += measurements(w);
         }
         c->st = known;
         if (n_syncs) *n_syncs = n_done;
         return status != ADPSGD_OK ? status : ok();
     }
+
+    if (n_steps > 0 && control) {
+        *c->h_sched = SchedState{known.t, known.cnt, known.nC2, known.C2, known.p, 0};
+        HIP_TRY(hipMemcpyAsync(c->d_sched, c->h_sched, sizeof(SchedState), hipMemcpyHostToDevice, c->stream));
+    }
+
+    // Account for every launch at the front that is finished (with `wait`, for
+    // at least the first one that has records).
+    auto drain = [&](bool wait) -> int {
+        while (!inflight.empty()) {
+            const Entry e = inflight.front();
+            if (e.slot0 >= 0) {
+                const hipEvent_t ev = c->ring_ev[(e.slot0 + e.n_slots - 1) % kRing];
+                hipError_t q;
+                if (wait) {
+                    Range wait_("adpsgd_run: wait for a record");
+                    q = hipEventSynchronize(ev);
+                } else {
+                    q = hipEventQuery(ev);
+                }
+                if (q == hipErrorNotReady) break;
+                if (q != hipSuccess) return hip_fail(q, "wait for a record");
+                wait = false;
+                slots_used -= e.n_slots;
+                dirty = true;
+            }
+            inflight.pop_front();
+            const int rc = account(e);
+            if (rc && status == ADPSGD_OK) status = rc;
+        }
+        return ADPSGD_OK;
+    };
+
+    // The schedule after every launch in flight, as far as the host knows it: st
+    // exactly; exactly but for p, which a decision in flight may move by one
+    // (p_open); or only that the next step lies in [st.t, t_hi], behind n_open
+    // launches that the device ends after decisions in flight.
+    struct Ahead { adpsgd_state st; int64_t t_hi; bool p_open; int n_open; };
+    auto pass = [&](Ahead *a, const SpanWhen &w) {
+        if (by_step) {
+            a->t_hi = ++a->st.t;
+        } else if (w.device && (a->p_open || a->n_open > 0)) {
+            a->n_open += 1;
+            a->t_hi = std::min(end, a->t_hi + w.n);
+        } else {
+            for (int32_t j = 0; j < w.n && a->st.t < end; ++j) {
+                const int64_t t = a->st.t;
+                const bool due = plan_step(rule, &a->st);
+                a->p_open = a->p_open || (due && sync_decisive(rule, t));
+                if (due && w.device) break;
+            }
+            a->t_hi = a->st.t;
+        }
+    };
+    Ahead ahead{known, known.t, false, 0};
+
     int hard = ADPSGD_OK;  // a HIP failure: stop at once
     while (hard == ADPSGD_OK) {
         if (n_launches % kPollEvery == 0) {
             if ((hard = drain(false))) break;
             if (c->timing && (hard = harvest(c, false))) break;
         }
-        if (launched == end || status != ADPSGD_OK) {
+        if (dirty) {
+            ahead = Ahead{known, known.t, false, 0};
+            for (const Entry &e : inflight) pass(&ahead, e.w);
+            dirty = false;
+        }
+        const adpsgd_state &pl = ahead.st;
+        if (status != ADPSGD_OK || ahead.t_hi >= end) {
+            // (launches the device ends may stop short of the end: then there is more to do)
             if (inflight.empty()) break;
             hard = drain(true);
             continue;
         }
-        if (dirty) {
-            plan = Plan{true, known.cnt, known.p, known.p};
-            for (const Entry &e : inflight)
-                for (int32_t j = 0; j < e.n; ++j) (void)advance(plan, e.t + j);
-            dirty = false;
-        }
-        Plan next = plan;
-        Cls cls = advance(next, launched);
-        if (traced || c->policy == ADPSGD_LAUNCH_DEVICE) cls = cDue;
-        bool wait = (int64_t)inflight.size() >= kMaxInflight || (cls != cPlain && n_dev >= kRing);
-        if (cls == cUncertain && !wait) {
-            // steps queued on the GPU behind the oldest record not yet read
-            int64_t behind = 0;
-            bool seen_dev = false;
-            for (const Entry &q : inflight) {
-                if (seen_dev) ++behind;
-                seen_dev = seen_dev || q.dev;
+
+        Entry e{SpanWhen{}, -1, 0, -1};
+        bool wait = false;
+        if (by_step) {
+            // one step at a time, decided by the device
+            e.w = SpanWhen{pl.t, end, 0, 1, 1, 1, traced ? 1 : 0};
+        } else if (!ahead.p_open && ahead.n_open == 0) {
+            adpsgd_state to = pl;
+            e.w = plan_span(c, &to, end, traced);
+        } else if (c->policy == ADPSGD_LAUNCH_HOST || ahead.n_open >= kMaxOpen) {
+            wait = true;
+        } else {
+            // a span the device ends, of at most as many steps as the longest
+            // period that the decisions in flight allow
+            const bool at_t = ahead.n_open == 0;
+            const int64_t p_hi = std::min<int64_t>(rule.p_max, (int64_t)pl.p + 1 + ahead.n_open);
+            int64_t most = std::max<int64_t>(1, p_hi - (at_t ? pl.cnt : 0));
+            most = std::min(most, end - pl.t);
+            if (traced) most = std::min<int64_t>(most, c->n_slots);
+            if (!span_in_registers(c->K)) {
+                most = 1;
+                wait = !at_t;
             }
-            wait = c->policy == ADPSGD_LAUNCH_HOST || behind >= kQueueToWait || n_uncertain >= kMaxUncertain;
+            if (at_t) most = std::min<int64_t>(most, kSpanSteps);
+            else if (ahead.t_hi - pl.t + most > kSpanSteps) wait = true;   // the rates it may need do not fit
+            e.w = SpanWhen{pl.t, end, 0, (int32_t)std::min<int64_t>(most, kSpanSteps), 1, at_t ? 1 : 0, traced ? 1 : 0};
+        }
+        if (!wait) {
+            e.n_slots = measurements(e.w);
+            wait = slots_used + e.n_slots > kRing || (int64_t)inflight.size() >= kMaxInflight;
         }
         if (wait) {
-            // account for the plain entries at the front and wait for the
-            // first device-decided one (with nothing in flight the plan is
-            // exact, so there is always something to wait for)
             if (inflight.empty()) { hard = fail(ADPSGD_ESTATE, "internal: nothing in flight to wait for"); break; }
             hard = drain(true);
             continue;
         }
-        Entry e{launched, cls != cPlain, cls == cUncertain, -1, -1, 1};
-        if (cls == cPlain) {
-            // with the plain steps that follow it, in one launch
-            for (Plan more = next; e.n < kSpanSteps && launched + e.n < end; ++e.n) {
-                if (advance(more, launched + e.n) != cPlain) break;
-                next = more;
-            }
-            hard = enqueue_steps(c, launched, e.n);
+        if (e.n_slots == 0) {
+            hard = enqueue_steps(c, e.w.t, e.w.n);
         } else {
-            // a sync the host planned runs the fused kernel; the device's reduction
-            // still confirms it and takes the decision
-            const int mode = traced ? kDeviceTrace
-                                    : (cls == cDue && c->policy != ADPSGD_LAUNCH_DEVICE) ? kFused : kDevice;
-            e.slot = (int)(n_slots++ % kRing);
-            hard = enqueue_sync(c, mode, launched, e.slot, true, &e.seq);
-            ++n_dev;
-            if (e.uncertain) ++n_uncertain;
+            e.slot0 = (int)(next_slot % kRing);
+            next_slot += e.n_slots;
+            slots_used += e.n_slots;
+            hard = enqueue_span(c, e.w, e.slot0, control, &e.seq);
         }
         if (hard) break;
         inflight.push_back(e);
-        plan = next;
-        launched += e.n;
+        pass(&ahead, e.w);
         ++n_launches;
     }
     // whatever was enqueued runs to completion and is accounted for
     hipError_t e = hipStreamSynchronize(c->stream);
-    if (e == hipSuccess && hard == ADPSGD_OK) hard = drain(true);
-    if (e == hipSuccess && hard == ADPSGD_OK)
-        while (!inflight.empty() && hard == ADPSGD_OK) hard = drain(true);
+    while (e == hipSuccess && hard == ADPSGD_OK && !inflight.empty()) hard = drain(true);
     c->st = known;
     if (n_syncs) *n_syncs = n_done;
     if (hard != ADPSGD_OK) return hard;

@@ -89,6 +89,48 @@ ADPSGD_HD bool apply_sync(const SchedRule &r, int64_t t, double gamma, double S,
     return true;
 }
 
+// Which steps a launch takes and which of them a sync follows.  The host plans
+// both (device = 0: steps t .. t + n - 1, bit j of syncs set when a sync follows
+// step t + j), or the launch ends with the first step that the device's
+// controller state says is due, after n steps or before step `end`, whichever
+// comes first; it starts at t (known) or at the state's next step, which is then
+// at most kSpanSteps - 1 beyond t, the step of the launch's first rate.
+constexpr int kSpanSteps = 64;   // steps per launch at most
+struct SpanWhen {
+    int64_t t;
+    int64_t end;
+    uint64_t syncs;
+    int32_t n;
+    int32_t device;
+    int32_t known;
+    int32_t measure;   // 1: every step is measured, not only those a sync follows
+};
+struct SpanPlan {
+    int64_t t;         // the first step
+    int32_t n;         // steps (0: nothing is left to do)
+    uint64_t syncs;
+};
+
+// The controller state is the device's at the start of the launch (read by
+// every thread, written only by the reduction that follows), so the answer is
+// uniform over the launch and its reduction.
+ADPSGD_HD SpanPlan span_plan(const SpanWhen &w, const SchedState *sched, const SchedRule &r) {
+    if (!w.device) return SpanPlan{w.t, w.n, w.syncs};
+    const SchedState s = *sched;
+    SpanPlan p{w.known ? w.t : s.t, 0, 0};
+    int64_t most = w.n < kSpanSteps - (p.t - w.t) ? w.n : kSpanSteps - (p.t - w.t);
+    if (most > w.end - p.t) most = w.end - p.t;
+    for (int64_t cnt = s.cnt + (p.t - s.t); p.n < most;) {
+        const int64_t t = p.t + p.n;
+        ++p.n;
+        if (sync_due(r, ++cnt, period_at(r, s.p, t), t)) {
+            p.syncs = uint64_t(1) << (p.n - 1);
+            break;
+        }
+    }
+    return p;
+}
+
 #undef ADPSGD_HD
 
 }  // namespace adpsgd

@@ -38,3 +38,77 @@ def test_steps_of_one_call_equal_single_steps(A, n, sizes, pad):
         assert np.array_equal(a.m.cpu().numpy(), b.m.cpu().numpy())
         sa, sb = a.get_state(), b.get_state()
         assert (sa.t, sa.cnt) == (sb.t, sb.cnt) == (n, n)
+
+
+def _by_hand(A, w, n, pad=True):
+    """n steps one launch of one step at a time: the schedule from the host
+    controller, each sync the one-step fused call."""
+    st = A.adpsgd_sched_init(A.hparams_of(w))
+    syncs, var = [], []
+    with A.Adpsgd.from_workload(w, pad_rows=pad) as eng:
+        for _ in range(n):
+            t = st.t
+            if A.adpsgd_sched_step(eng.hp, st):
+                v = eng.step_average()
+                A.adpsgd_sched_on_sync(eng.hp, st, t, float(sum(v)))
+                syncs.append(t)
+                var.append(v)
+            else:
+                eng.local_steps(1)
+        return eng.x.cpu().numpy(), eng.m.cpu().numpy(), syncs, np.asarray(var)
+
+
+# worker counts of every layout: compiled (one row per wave, and several with
+# enough chunks), K an argument with 1, 2, 4 and 8 rows per wave (whole and
+# ragged last waves), the loop kernel; 140,000 elements give every tall layout
+# two waves per SIMD, 3,000 none
+@pytest.mark.parametrize("avg_m", [False, True])
+@pytest.mark.parametrize("K,P", [(1, 3000), (2, 530_001), (4, 270_001), (8, 140_001), (16, 140_001), (32, 70_001), (8, 3000),
+                                 (32, 3000), (3, 9001), (7, 9001), (24, 9001), (33, 5001), (64, 5001), (65, 3001),
+                                 (100, 3001), (128, 3000), (129, 2001)])
+def test_run_equals_one_step_launches(A, K, P, avg_m):
+    """A constant-period run (whole spans of syncs) against single-step launches:
+    the replicas and momenta bit for bit, the variances to the rounding of
+    their sums, with tensors that begin inside a chunk."""
+    w = _w(K=K, sizes=(700, 1, 3, 0, 280, P - 984), p_init=3, total_steps=40, avg_momentum=avg_m)
+    n = 23
+    x, m, syncs, var = _by_hand(A, w, n)
+    with A.Adpsgd.from_workload(w) as eng:
+        recs, v, _ = eng.run(n)
+        assert list(recs["t"]) == syncs
+        assert np.array_equal(eng.x.cpu().numpy(), x) and np.array_equal(eng.m.cpu().numpy(), m)
+    assert np.allclose(v, var, rtol=1e-12, atol=0.0)
+
+
+@pytest.mark.parametrize("K,pad", [(4, False), (8, True), (5, False), (100, False)])
+def test_unaligned_and_cut_rows(A, K, pad):
+    """Packed rows of a length that is not a multiple of 4, and a last chunk cut
+    inside a group, in launches of several steps and syncs."""
+    w = _w(K=K, sizes=(255, 2, 257, 1301), p_init=2, total_steps=40)
+    x, m, syncs, var = _by_hand(A, w, 17, pad)
+    with A.Adpsgd.from_workload(w, pad_rows=pad) as eng:
+        recs, v, _ = eng.run(17)
+        assert np.array_equal(eng.x.cpu().numpy(), x) and np.array_equal(eng.m.cpu().numpy(), m)
+    assert list(recs["t"]) == syncs and np.allclose(v, var, rtol=1e-12, atol=0.0)
+
+
+# periods around the most steps (64) and measurements (16) of a launch; K = 129
+# steps one at a time where the device decides
+@pytest.mark.parametrize("traced", [False, True])
+@pytest.mark.parametrize("K,p,N", [(4, 1, 90), (4, 15, 120), (8, 17, 150), (4, 63, 300), (8, 64, 300), (4, 66, 340),
+                                   (8, 130, 500), (129, 3, 40)])
+def test_adaptive_periods_agree_under_every_policy(A, K, p, N, traced):
+    """Adaptive runs whose period moves (a decisive sync from the second on): the
+    default driver's spans, single device-decided steps and host-planned
+    spans give the same records and bits."""
+    w = _w(K=K, sizes=(2000, 7, 1500), p_init=p, total_steps=N, period_mode=W.PERIOD_ADAPTIVE, k_s=p,
+           lr_kind=W.LR_STEP)
+    out = []
+    for pol in (A.LAUNCH_HYBRID, A.LAUNCH_DEVICE, A.LAUNCH_HOST):
+        with A.Adpsgd.from_workload(w) as eng:
+            eng.set_launch_policy(pol)
+            r = eng.run_traced(N) if traced else eng.run(N)
+            st = eng.get_state()
+            out.append((r[0].tobytes(), r[1].tobytes(), r[3].tobytes() if traced else b"", eng.x.cpu().numpy().tobytes(),
+                        eng.m.cpu().numpy().tobytes(), (st.t, st.cnt, st.p, st.nC2, st.C2)))
+    assert len(r[0]) > 1 and out[0] == out[1] == out[2]
