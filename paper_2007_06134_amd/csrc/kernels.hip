@@ -623,14 +623,20 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT
     // uniform row addresses (the lane's offset is 32 bits)
     float *const xb = a.x + (int64_t)(R * w) * a.ld + lo;
     float *const mb = a.m + (int64_t)(R * w) * a.ld + lo;
+    // merged rows: row 0 for all, from the cache for all waves but one
+    const bool x_one = sp.merged_in, m_one = sp.merged_in && p.avg_m;
     f4 x[R], m[R], h, xs;
     if (whole) {
+        if (x_one) x[0] = ld4<false>(a.x + lo + e);
+        if (m_one) m[0] = ld4<false>(a.m + lo + e);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            x[r] = m[r] = splat(0.0f);
-            if (!has[r]) continue;
-            x[r] = ld4<NT>(xb + r * a.ld + e);
-            m[r] = ld4<NT>(mb + r * a.ld + e);
+            if (!has[r]) {
+                x[r] = m[r] = splat(0.0f);
+                continue;
+            }
+            x[r] = x_one ? x[0] : ld4<NT>(xb + r * a.ld + e);
+            m[r] = m_one ? m[0] : ld4<NT>(mb + r * a.ld + e);
         }
         h = ld4<false>(a.h + lo + e);
         xs = ld4<false>(a.xs + lo + e);
@@ -639,8 +645,10 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT
         for (int r = 0; r < R; ++r) {
             x[r] = m[r] = splat(0.0f);
             if (!has[r]) continue;
-            x[r] = full ? ld4<NT>(xb + r * a.ld + e) : ld4_left(xb + r * a.ld + e, left);
-            m[r] = full ? ld4<NT>(mb + r * a.ld + e) : ld4_left(mb + r * a.ld + e, left);
+            const float *const xr = x_one ? a.x + lo + e : xb + r * a.ld + e;
+            const float *const mr = m_one ? a.m + lo + e : mb + r * a.ld + e;
+            x[r] = full ? ld4<NT>(xr) : ld4_left(xr, left);
+            m[r] = full ? ld4<NT>(mr) : ld4_left(mr, left);
         }
         // (h and x* are aligned whatever the rows' stride)
         h = left >= 4 ? ld4<false>(a.h + lo + e) : ld4_left(a.h + lo + e, left);
@@ -738,19 +746,26 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT
         }
         ++slot;
     }
-    if (whole) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (!has[r]) continue;
-            st4<NT>(xb + r * a.ld + e, x[r]);
-            st4<NT>(mb + r * a.ld + e, m[r]);
+    if constexpr (WMAX > 1) {
+        // every wave has read the merged row before one writes it (a measurement's
+        // barriers, which come after the steps that used it, see to that too)
+        if (sp.merged_in && sp.syncs == 0 && !p.when.measure) {
+            asm volatile("" ::"v"(x[0].x), "v"(m[0].x));
+            __syncthreads();
         }
-    } else {
+    }
+    // (row 0 alone where the launch leaves merged rows)
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (!has[r]) continue;
-            if (full) st4<NT>(xb + r * a.ld + e, x[r]); else st4_left(xb + r * a.ld + e, x[r], left);
-            if (full) st4<NT>(mb + r * a.ld + e, m[r]); else st4_left(mb + r * a.ld + e, m[r], left);
+    for (int r = 0; r < R; ++r) {
+        if (!has[r]) continue;
+        const bool lead = R * w + r == 0;   // uniform
+        const bool x_out = lead || !sp.merged_out, m_out = lead || !(sp.merged_out && p.avg_m);
+        if (whole) {
+            if (x_out) st4<NT>(xb + r * a.ld + e, x[r]);
+            if (m_out) st4<NT>(mb + r * a.ld + e, m[r]);
+        } else {
+            if (x_out) { if (full) st4<NT>(xb + r * a.ld + e, x[r]); else st4_left(xb + r * a.ld + e, x[r], left); }
+            if (m_out) { if (full) st4<NT>(mb + r * a.ld + e, m[r]); else st4_left(mb + r * a.ld + e, m[r], left); }
         }
     }
 }
@@ -1191,6 +1206,18 @@ __global__ void __launch_bounds__(kBlock) k_zero_rows(float *a, int64_t ld, int6
     else st4_masked(row, splat(0.0f), e0, 0, P);
 }
 
+// Rows 1 .. K - 1 = row 0; thread = one float4 group of one row (from row 1 on).
+template <bool VEC>
+__global__ void __launch_bounds__(kBlock) k_spread_row(float *a, int64_t ld, int64_t P, int64_t groups_per_row,
+                                                       int64_t j0, int64_t n) {
+    const int64_t j = j0 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (j >= n) return;
+    const int64_t k = j / groups_per_row, e0 = 4 * (j - k * groups_per_row);
+    float *row = a + (k + 1) * ld + e0;
+    if (VEC && e0 + 4 <= P) st4<false>(row, ld4<false>(a + e0));
+    else st4_masked(row, ld4_masked(a + e0, e0, 0, P), e0, 0, P);
+}
+
 __global__ void __launch_bounds__(kBlock) k_philox_dump(RoundKeys rk, uint32_t c1, uint32_t c2, uint32_t c3,
                                                         int64_t g0, int64_t n, uint32_t *out) {
     const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -1523,6 +1550,15 @@ hipError_t launch_zero_rows(float *a, int64_t ld, int64_t P, int32_t K, bool vec
     return groups_in_pieces(n, [&](int64_t j0, int64_t, unsigned nb) {
         if (vec) k_zero_rows<true><<<dim3(nb), dim3(kBlock), 0, st>>>(a, ld, P, gpr, j0, n);
         else k_zero_rows<false><<<dim3(nb), dim3(kBlock), 0, st>>>(a, ld, P, gpr, j0, n);
+    });
+}
+
+hipError_t launch_spread_row(float *a, int64_t ld, int64_t P, int32_t K, bool vec, hipStream_t st) {
+    if (P <= 0 || K <= 1) return hipSuccess;
+    const int64_t gpr = (P + 3) / 4, n = gpr * (K - 1);
+    return groups_in_pieces(n, [&](int64_t j0, int64_t, unsigned nb) {
+        if (vec) k_spread_row<true><<<dim3(nb), dim3(kBlock), 0, st>>>(a, ld, P, gpr, j0, n);
+        else k_spread_row<false><<<dim3(nb), dim3(kBlock), 0, st>>>(a, ld, P, gpr, j0, n);
     });
 }
 

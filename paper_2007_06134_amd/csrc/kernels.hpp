@@ -208,6 +208,8 @@ hipError_t launch_reduce(const ReduceParams &r, hipStream_t st);
 // Zero elements [0, P) of each of the K rows of a (rows ld apart); vec: ld is
 // a multiple of 4 and a 16-byte aligned, so whole groups take one store.
 hipError_t launch_zero_rows(float *a, int64_t ld, int64_t P, int32_t K, bool vec, hipStream_t st);
+// Copy row 0's elements [0, P) to the other K - 1 rows.
+hipError_t launch_spread_row(float *a, int64_t ld, int64_t P, int32_t K, bool vec, hipStream_t st);
 hipError_t launch_init_problem(float *h, float *xs, int64_t P, uint64_t seed, double h_lo,
                                double h_hi, hipStream_t st);
 hipError_t launch_philox_dump(uint64_t seed, uint32_t c1, uint32_t c2, uint32_t c3, int64_t g0,

@@ -451,7 +451,7 @@ SyncParams sync_params(const adpsgd_ctx *c) {
 // A span the host planned: steps t .. t + n - 1, bit j of syncs set when a sync
 // follows step t + j; measure: every step is measured.
 SpanWhen planned(int64_t t, int32_t n, uint64_t syncs, bool measure) {
-    return SpanWhen{t, t + n, syncs, n, 0, 1, measure ? 1 : 0};
+    return SpanWhen{t, t + n, syncs, n, 0, 1, measure ? 1 : 0, 0, 0};
 }
 int measurements(const SpanWhen &w) {
     if (w.measure) return w.n;
@@ -535,12 +535,12 @@ int enqueue_sync(adpsgd_ctx *c, bool average, int64_t t) {
     return ok();
 }
 
-// A span, then the reduction of its measurements into the record slots from
-// `slot0` on, then the event of the last of them.  *seq: the timed sequence
+// A span, then the reduction of its measurements (if any) into the record slots
+// from `slot0` on, then the event of the last of them.  *seq: the timed sequence
 // number of the span.
 int enqueue_span(adpsgd_ctx *c, const SpanWhen &w, int slot0, bool control, int64_t *seq) {
     int rc = timed_launch(c, -1, [&] { return launch_span_of(c, w, c->sync_nt, c->stream); }, seq, w.n);
-    if (rc) return rc;
+    if (rc || measurements(w) == 0) return rc;
     const ReduceParams r = reduce_params(c, w, c->d_slots, slot0, kRing, control);
     rc = timed_launch(c, tSegsum, [&] { return launch_reduce(r, c->stream); }, nullptr, r.n_slots);
     if (rc) return rc;
@@ -563,9 +563,13 @@ bool plan_step(const SchedRule &rule, adpsgd_state *st) {
 // `end`, ending after the last sync that fits n_slots (every step needs a slot
 // when all are measured), after a sync whose outcome may move p, or at the end.
 // Without measurements it is plain steps.  st is moved to the state after it.
-SpanWhen plan_span(const adpsgd_ctx *c, adpsgd_state *st, int64_t end, bool measure) {
+// merge: launches of the run leave merged rows at syncs; merged: one did.
+SpanWhen plan_span(const adpsgd_ctx *c, adpsgd_state *st, int64_t end, bool measure, bool merge, bool merged) {
     const SchedRule rule = rule_of(&c->hp);
     SpanWhen w = planned(st->t, 0, 0, measure);
+    w.end = end;
+    w.merge = merge ? 1 : 0;
+    w.merged = merged ? 1 : 0;
     int slots = 0;
     adpsgd_state after_sync = *st;   // the state after the last sync of the span
     int32_t n_sync = 0;
@@ -587,7 +591,6 @@ SpanWhen plan_span(const adpsgd_ctx *c, adpsgd_state *st, int64_t end, bool meas
         *st = after_sync;
         w.n = n_sync;
     }
-    w.end = w.t + w.n;
     return w;
 }
 
@@ -611,11 +614,11 @@ int capture_run(adpsgd_ctx *c, const std::vector<SpanWhen> &spans, int64_t n_syn
     int slot = 0;
     for (const SpanWhen &w : spans) {
         const int m = measurements(w);
-        if (m == 0) {
+        if (m == 0 && !w.merged) {
             e = launch_local_step(step_params(c, w.t, w.n), c->vec, c->nontemporal, c->step_shape, cs);
         } else {
             e = launch_span_of(c, w, c->sync_nt, cs);
-            if (e == hipSuccess)
+            if (e == hipSuccess && m > 0)
                 e = launch_reduce(reduce_params(c, w, c->d_gslots, slot, (int)std::max<int64_t>(n_sync, 1), false), cs);
         }
         slot += m;
@@ -1039,6 +1042,7 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
     const bool adaptive = hp.period_mode == ADPSGD_PERIOD_ADAPTIVE;
     const bool by_step = c->policy == ADPSGD_LAUNCH_DEVICE;   // every step decided on the device
     const bool control = adaptive || by_step;   // the controller state lives on the device
+    const bool merge = !by_step && c->K > 1 && span_in_registers(c->K);
     const int64_t t0 = c->st.t, end = t0 + n_steps;
 
     // A run whose schedule is fixed in advance (constant-period modes) on a
@@ -1123,7 +1127,7 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
         adpsgd_state pl = known;
         int64_t n_sync = 0;
         while (pl.t < end) {
-            spans.push_back(plan_span(c, &pl, end, false));
+            spans.push_back(plan_span(c, &pl, end, false, merge, merge && !spans.empty() && pl.cnt == 0));
             n_sync += measurements(spans.back());
         }
         const int64_t key[7] = {t0, n_steps, known.cnt, known.p, c->step_shape.block, c->step_shape.lds,
@@ -1229,10 +1233,11 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
         bool wait = false;
         if (by_step) {
             // one step at a time, decided by the device
-            e.w = SpanWhen{pl.t, end, 0, 1, 1, 1, traced ? 1 : 0};
+            e.w = SpanWhen{pl.t, end, 0, 1, 1, 1, traced ? 1 : 0, 0, 0};
         } else if (!ahead.p_open && ahead.n_open == 0) {
             adpsgd_state to = pl;
-            e.w = plan_span(c, &to, end, traced);
+            // (at the start of a run the rows are the caller's)
+            e.w = plan_span(c, &to, end, traced, merge, merge && n_launches > 0 && pl.cnt == 0);
         } else if (c->policy == ADPSGD_LAUNCH_HOST || ahead.n_open >= kMaxOpen) {
             wait = true;
         } else {
@@ -1249,7 +1254,8 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
             }
             if (at_t) most = std::min<int64_t>(most, kSpanSteps);
             else if (ahead.t_hi - pl.t + most > kSpanSteps) wait = true;   // the rates it may need do not fit
-            e.w = SpanWhen{pl.t, end, 0, (int32_t)std::min<int64_t>(most, kSpanSteps), 1, at_t ? 1 : 0, traced ? 1 : 0};
+            e.w = SpanWhen{pl.t, end, 0, (int32_t)std::min<int64_t>(most, kSpanSteps), 1, at_t ? 1 : 0, traced ? 1 : 0,
+                           merge ? 1 : 0, 0};
         }
         if (!wait) {
             e.n_slots = measurements(e.w);
@@ -1260,8 +1266,10 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
             hard = drain(true);
             continue;
         }
-        if (e.n_slots == 0) {
+        if (e.n_slots == 0 && !e.w.merged) {
             hard = enqueue_steps(c, e.w.t, e.w.n);
+        } else if (e.n_slots == 0) {
+            hard = enqueue_span(c, e.w, 0, control, &e.seq);
         } else {
             e.slot0 = (int)(next_slot % kRing);
             next_slot += e.n_slots;
@@ -1276,6 +1284,13 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
     // whatever was enqueued runs to completion and is accounted for
     hipError_t e = hipStreamSynchronize(c->stream);
     while (e == hipSuccess && hard == ADPSGD_OK && !inflight.empty()) hard = drain(true);
+    if (e == hipSuccess && hard == ADPSGD_OK && merge && n_launches > 0 && known.t < end && known.cnt == 0) {
+        // stopped by a non-finite S behind a sync: whole rows again
+        e = launch_spread_row(c->buf.x, c->ld, c->P, c->K, c->vec, c->stream);
+        if (e == hipSuccess && hp.avg_momentum)
+            e = launch_spread_row(c->buf.m, c->ld, c->P, c->K, c->vec, c->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    }
     c->st = known;
     if (n_syncs) *n_syncs = n_done;
     if (hard != ADPSGD_OK) return hard;

@@ -96,18 +96,26 @@ ADPSGD_HD bool apply_sync(const SchedRule &r, int64_t t, double gamma, double S,
 // comes first; it starts at t (known) or at the state's next step, which is then
 // at most kSpanSteps - 1 beyond t, the step of the launch's first rate.
 constexpr int kSpanSteps = 64;   // steps per launch at most
+//
+// Merged rows: behind a sync the K rows of x are equal (and of m, where momentum
+// is averaged), so inside a run a launch that ends with a sync writes row 0
+// alone and the next one reads row 0 for all.  Every launch with a sync of such
+// a run does so (merge), except that the run's last step leaves whole rows.
 struct SpanWhen {
     int64_t t;
-    int64_t end;
+    int64_t end;       // the run's end
     uint64_t syncs;
     int32_t n;
     int32_t device;
     int32_t known;
     int32_t measure;   // 1: every step is measured, not only those a sync follows
+    int32_t merge;     // 1: a sync at the launch's end leaves merged rows
+    int32_t merged;    // (host-planned) the rows are merged at the start
 };
 struct SpanPlan {
     int64_t t;         // the first step
     int32_t n;         // steps (0: nothing is left to do)
+    bool merged_in, merged_out;
     uint64_t syncs;
 };
 
@@ -115,19 +123,26 @@ struct SpanPlan {
 // every thread, written only by the reduction that follows), so the answer is
 // uniform over the launch and its reduction.
 ADPSGD_HD SpanPlan span_plan(const SpanWhen &w, const SchedState *sched, const SchedRule &r) {
-    if (!w.device) return SpanPlan{w.t, w.n, w.syncs};
-    const SchedState s = *sched;
-    SpanPlan p{w.known ? w.t : s.t, 0, 0};
-    int64_t most = w.n < kSpanSteps - (p.t - w.t) ? w.n : kSpanSteps - (p.t - w.t);
-    if (most > w.end - p.t) most = w.end - p.t;
-    for (int64_t cnt = s.cnt + (p.t - s.t); p.n < most;) {
-        const int64_t t = p.t + p.n;
-        ++p.n;
-        if (sync_due(r, ++cnt, period_at(r, s.p, t), t)) {
-            p.syncs = uint64_t(1) << (p.n - 1);
-            break;
+    SpanPlan p{w.t, w.n, w.merged != 0, false, w.syncs};
+    if (w.device) {
+        const SchedState s = *sched;
+        if (!w.known) p.t = s.t;
+        p.n = 0;
+        p.syncs = 0;
+        int64_t most = w.n < kSpanSteps - (p.t - w.t) ? w.n : kSpanSteps - (p.t - w.t);
+        if (most > w.end - p.t) most = w.end - p.t;
+        int64_t cnt = s.cnt + (p.t - s.t);
+        p.merged_in = w.merge && cnt == 0;   // (a launch of the run ended with the last sync)
+        while (p.n < most) {
+            const int64_t t = p.t + p.n;
+            ++p.n;
+            if (sync_due(r, ++cnt, period_at(r, s.p, t), t)) {
+                p.syncs = uint64_t(1) << (p.n - 1);
+                break;
+            }
         }
     }
+    p.merged_out = w.merge && p.n > 0 && ((p.syncs >> (p.n - 1)) & 1) && p.t + p.n < w.end;
     return p;
 }
 

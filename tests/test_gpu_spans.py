@@ -112,3 +112,45 @@ def test_adaptive_periods_agree_under_every_policy(A, K, p, N, traced):
             out.append((r[0].tobytes(), r[1].tobytes(), r[3].tobytes() if traced else b"", eng.x.cpu().numpy().tobytes(),
                         eng.m.cpu().numpy().tobytes(), (st.t, st.cnt, st.p, st.nC2, st.C2)))
     assert len(r[0]) > 1 and out[0] == out[1] == out[2]
+
+
+@pytest.mark.parametrize("avg_m", [False, True])
+@pytest.mark.parametrize("K,mode,pol", [(4, W.PERIOD_CONST, "HYBRID"), (8, W.PERIOD_ADAPTIVE, "HYBRID"),
+                                        (5, W.PERIOD_ADAPTIVE, "HOST"), (16, W.PERIOD_ALG1, "HYBRID")])
+def test_rows_are_whole_between_runs(A, K, mode, pol, avg_m):
+    """Inside a run the rows behind a sync are kept once.  Runs cut anywhere, at
+    a sync, behind one and in a period, with the rows changed by the caller in
+    between, equal the same steps launched one by one."""
+    w = _w(K=K, sizes=(3000, 5, 600), p_init=3, total_steps=200, avg_momentum=avg_m, period_mode=mode,
+           k_s=6 if mode == W.PERIOD_ADAPTIVE else 0)
+    cuts = [3, 1, 2, 4, 6, 7, 80, 3]
+    with A.Adpsgd.from_workload(w) as a, A.Adpsgd.from_workload(w) as b:
+        a.set_launch_policy(getattr(A, "LAUNCH_" + pol))
+        for i, n in enumerate(cuts):
+            a.run(n)
+            st = b.get_state()
+            for _ in range(n):
+                t = st.t
+                if A.adpsgd_sched_step(b.hp, st):
+                    v = b.step_average()
+                    A.adpsgd_sched_on_sync(b.hp, st, t, float(sum(v)))
+                    b.set_state(st)
+                else:
+                    b.local_steps(1)
+            assert np.array_equal(a.x.cpu().numpy(), b.x.cpu().numpy()), (i, n)
+            assert np.array_equal(a.m.cpu().numpy(), b.m.cpu().numpy()), (i, n)
+            a.x[K - 1].add_(0.01 * (i + 1))       # the caller's own change, to one row
+            b.x[K - 1].add_(0.01 * (i + 1))
+
+
+def test_rows_are_whole_after_a_failed_sync(A):
+    """A run that a non-finite S stops behind a sync leaves whole rows."""
+    w = _w(K=4, sizes=(3000, 5), lr_kind=W.LR_CONST, lr0=50.0, p_init=2, total_steps=300, period_mode=W.PERIOD_ADAPTIVE)
+    with A.Adpsgd.from_workload(w) as eng:
+        with pytest.raises(A.AdpsgdError) as e:
+            eng.run(300)
+        assert e.value.code == A.ENONFINITE
+        st = eng.get_state()
+        x = eng.x.cpu().numpy()
+    assert st.cnt == 0 and st.t < 300          # stopped behind a sync
+    assert all(np.array_equal(x[k], x[0], equal_nan=True) for k in range(4))
