@@ -29,6 +29,7 @@
 // given (K, P, offsets).
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -54,6 +55,12 @@ __device__ __forceinline__ f4 fma4(f4 a, f4 b, f4 c) {
     return f4{fmaf(a.x, b.x, c.x), fmaf(a.y, b.y, c.y), fmaf(a.z, b.z, c.z), fmaf(a.w, b.w, c.w)};
 }
 __device__ __forceinline__ f4 splat(float v) { return f4{v, v, v, v}; }
+// v, of which the compiler knows nothing.
+__device__ __forceinline__ f4 opaque(f4 v) {
+    float a = v.x, b = v.y, c = v.z, d = v.w;
+    asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+    return f4{a, b, c, d};
+}
 
 // Replica rows are touched once per step and never reused before the next
 // step, so with a working set beyond the on-chip caches they are streamed with
@@ -91,12 +98,24 @@ __device__ __forceinline__ f4 mask4(f4 v, int64_t e0, int64_t lo, int64_t hi) {
 }
 
 // What a lane keeps of its group over workers and steps.
+template <int ROUNDS>
 struct GroupData {
     f4 hw, xs, wxs;   // h + wd, x*, wd x*
     PhiloxGroup pg;
+    NoiseKeys<ROUNDS> keys;
+    float sigma_r, mu;   // of the launch, in vector registers
 };
-__device__ __forceinline__ GroupData group_data(const StepParams &a, int64_t g, f4 h, f4 xs) {
-    return GroupData{h + splat(a.wd), xs, splat(a.wd) * xs, philox_group((uint32_t)g, a.rk)};
+template <int ROUNDS>
+__device__ __forceinline__ GroupData<ROUNDS> group_data(const StepParams &a, int64_t g, f4 h, f4 xs) {
+    return GroupData<ROUNDS>{h + splat(a.wd), xs, splat(a.wd) * xs, philox_group((uint32_t)g, a.rk),
+                             noise_keys<ROUNDS>(a.rk), in_vgpr(a.sigma_r), in_vgpr(a.mu)};
+}
+
+// v = mu v + d in v's own register: left to itself the compiler adds into d's, and
+// copies all of m in every step of a loop.
+__device__ __forceinline__ float scale_add(float v, float mu, float d) {
+    asm("v_fma_f32 %0, %0, %1, %2" : "+v"(v) : "v"(mu), "v"(d));
+    return v;
 }
 
 // Step t + j of worker k: momentum SGD on the noisy quadratic, PyTorch-SGD form
@@ -105,13 +124,14 @@ __device__ __forceinline__ GroupData group_data(const StepParams &a, int64_t g, 
 // operations an element instead of seven, and no sum of it cancels that did not
 // before.  k is uniform over the wave.  Explicit fmaf fixes the rounding so
 // every kernel computes identical bits.
-// 8 steps at K = 8, P = 138M take 5.0 ms with this and philox_noise, 6.0 ms with
-// ten rounds, two-input exclusive ors and the seven operations.
-__device__ __forceinline__ void sgd_step(const StepParams &a, const GroupData &gd, int k, f4 &x, f4 &m, int j = 0) {
-    const u4 r = philox_noise(gd.pg, (uint32_t)k, a.t + (uint32_t)j, a.rk);
-    const f4 d = fma4(gd.hw, x - gd.xs, add_noise4(a.sigma_r, r, gd.wxs));
-    m = fma4(splat(a.mu), m, d);
-    x = fma4(splat(-a.gamma[j]), m, x);
+// 64 steps at K = 16, P = 25.6M (k_local_step) take 10.7 ms; with the uniform
+// operands in scalar registers, conversions to float and m copied, 11.9.
+template <int ROUNDS>
+__device__ __forceinline__ void sgd_step(const StepParams &a, const GroupData<ROUNDS> &gd, int k, f4 &x, f4 &m, int j = 0) {
+    const u4 r = philox_noise(gd.pg, (uint32_t)k, a.t + (uint32_t)j, a.rk, gd.keys);
+    const f4 d = fma4(gd.hw, x - gd.xs, add_noise4(gd.sigma_r, r, gd.wxs));
+    m = f4{scale_add(m.x, gd.mu, d.x), scale_add(m.y, gd.mu, d.y), scale_add(m.z, gd.mu, d.z), scale_add(m.w, gd.mu, d.w)};
+    x = fma4(splat(in_vgpr(-a.gamma[j])), m, x);
 }
 
 // Sum of the squares of v's elements, in fp64.
@@ -187,7 +207,7 @@ __global__ void __launch_bounds__(BS) k_local_step(StepParams a) {
     if (VEC && (!TAIL || e0 + 4 <= a.P)) {
         f4 x = ld4<NT>(xr), m = ld4<NT>(mr);
         const f4 h = ld4<false>(a.h + e0), xs = ld4<false>(a.xs + e0);
-        const GroupData gd = group_data(a, g, h, xs);
+        const auto gd = group_data<8>(a, g, h, xs);
 #pragma unroll 1
         for (int j = 0; j < a.n; ++j) sgd_step(a, gd, k, x, m, j);
         st4<NT>(xr, x);
@@ -198,7 +218,7 @@ __global__ void __launch_bounds__(BS) k_local_step(StepParams a) {
         // to [0, P)
         f4 x = ld4_masked(xr, e0, 0, a.P), m = ld4_masked(mr, e0, 0, a.P);
         const f4 h = ld4_masked(a.h + e0, e0, 0, a.P), xs = ld4_masked(a.xs + e0, e0, 0, a.P);
-        const GroupData gd = group_data(a, g, h, xs);
+        const auto gd = group_data<8>(a, g, h, xs);
 #pragma unroll 1
         for (int j = 0; j < a.n; ++j) sgd_step(a, gd, k, x, m, j);
         st4_masked(xr, x, e0, 0, a.P);
@@ -561,12 +581,25 @@ constexpr int span_waves() {
     else return KT / R;
 }
 
+// Philox rounds whose keys k_span keeps in vector registers.  What decides is the
+// registers left: waves count for more than the keys do.  Measured with and
+// without: 400 steps at K = 32, P = 1.2M (eight rows a wave) 9.1 and 9.7 ms with the
+// keys of four rounds, but 32 steps at K = 8, P = 138M (eight rows, one wave a
+// block) 21.7 and 20.5 ms, and 100 at K = 16, P = 25.6M (four rows) 22.9 and 22.5
+// with one round's.  With one row a wave the launch is bound by HBM or by latency.
+template <int KT, int R>
+constexpr int span_vector_keys() {
+    if constexpr (KT == 0) return R < 8 ? 8 : 0;
+    else if constexpr (KT == 1) return 8;
+    else return KT == 32 && R == 8 ? 4 : 0;
+}
+
 // Waves per SIMD that k_span's registers leave room for, at least.
 template <int KT, int R>
 constexpr int span_occupancy() {
-    if constexpr (R == 1) return 8;
-    else if constexpr (R == 2) return KT > 0 ? (KT / R > 8 ? 8 : 7) : 6;
-    else if constexpr (KT > 0 && R == 4) return 5;
+    if constexpr (R == 1) return KT == 0 ? 6 : (KT == 1 ? 7 : 8);
+    else if constexpr (R == 2) return KT == 0 ? 5 : (KT == 32 ? 8 : 7);
+    else if constexpr (R == 4) return KT == 0 ? 4 : 5;
     else return 4;
 }
 
@@ -589,11 +622,11 @@ constexpr int span_occupancy() {
 // ends with the first step that Algorithm 2's counter, read from the device's
 // controller state, says is due (when.device; span_plan).
 //
-// Bound: a span of one step by HBM, of five and more by vector arithmetic, about
-// 290 cycles a wave and step.  At K = 8, P = 138M with the sync at the end, 1 / 2
-// / 4 / 8 steps take 3.09 / 3.13 / 3.24 / 5.0 ms (the steps one by one, then the
-// step with its sync: 3.05 / 6.0 / 11.9 / 23.7 ms); 64 steps with a sync every
-// eighth 32.8 ms, 0.51 ms a step.
+// Bound: a span of one step by HBM, of five and more by vector arithmetic: a row's
+// step is 73 instructions, among them 16 32-bit products (4 cycles a wave) and 8
+// transcendental functions (8 cycles), about 250 cycles of issue in all.  With the steps launched one by one, then in
+// spans of two rows a wave, then so: 32 steps at K = 8, P = 138M 96.8 / 25.4 / 21.1
+// ms, 24 traced at K = 8, P = 11.2M 6.41 / 1.94 / 1.48 ms.
 template <int KT, int R, bool VEC, bool NT>
 __global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT, R>())) k_span(SpanParams p) {
     constexpr int WMAX = span_waves<KT, R>();
@@ -657,7 +690,7 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT
     // the chunk's first tile and the next chunk's, in lanes 0 and 1: a vector
     // load, so that no wait for it comes ahead of the row loads
     const int32_t seg_l = p.chunk_seg[c + (lane & 1)];
-    const GroupData gd = group_data(a, g, h, xs);
+    const auto gd = group_data<span_vector_keys<KT, R>()>(a, g, h, xs);
     const int j0 = (int)(sp.t - p.when.t);   // the first step's rate is gamma[j0]
     int slot = 0;
 #pragma unroll 1
@@ -691,20 +724,17 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT
         const int32_t s0 = __builtin_amdgcn_readlane(seg_l, 0), s1 = __builtin_amdgcn_readlane(seg_l, 1);
         const bool summer = WMAX == 1 || w == (int)((uint32_t)(c + slot) % (uint32_t)W);
         double *const out = p.partials + (int64_t)slot * p.slot_stride;
-        // one sum per tile (tensor) of the chunk; usually all of the chunk is one
-        for (int32_t sgi = s0; sgi < s1; ++sgi) {
-            int begin = 0, n = len;
-            if (s1 - s0 > 1) {
-                const Tile t = p.tiles[sgi];
-                begin = (int)(t.start - lo);
-                n = t.len;
-            }
-            const bool cut = n < (int)kTileElems;   // uniform
+        // the sums of the chunk's elements [begin, begin + n) (CUT: not all 256) for tile sgi
+        auto tile_sums = [&](auto cut, int32_t sgi, int begin, int n) {
+            constexpr bool CUT = decltype(cut)::value;
+            // (opaque in a tile of several: the differences of all rows, formed once
+            // for every tile, would not stay in registers)
+            const f4 mean_t = CUT ? opaque(mean) : mean;
             double q[KT > 0 ? R : 1];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                f4 d = mean - x[r];
-                if (cut) d = mask4_range(d, e, begin, n);
+                f4 d = mean_t - x[r];
+                if (CUT) d = mask4_range(d, e, begin, n);
                 if constexpr (KT > 0) q[r] = square_sum(d);
                 else if (r == 0) q[0] = square_sum(d);   // (every wave has a first row)
                 else if (has[r]) q[0] += square_sum(d);
@@ -723,14 +753,14 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT
                         for (int i = 1; i < W; ++i) v += dev[i][lane];
                     }
                 }
-                if (s1 - s0 > 1) __syncthreads();   // dev is read before the next tile's sums
+                if (CUT) __syncthreads();   // dev is read before the next tile's sums
             }
             if (summer) {
                 v = wave_sum(v);
                 double gn = 0.0;
                 if (p.when.measure) {
-                    f4 gr = fma4(gd.hw, mean - gd.xs, gd.wxs);   // h (mean - x*) + wd mean
-                    if (cut) gr = mask4_range(gr, e, begin, n);
+                    f4 gr = fma4(gd.hw, mean_t - gd.xs, gd.wxs);   // h (mean - x*) + wd mean
+                    if (CUT) gr = mask4_range(gr, e, begin, n);
                     gn = wave_sum(square_sum(gr));
                 }
                 if (lane == 0) {
@@ -738,8 +768,19 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT
                     out[2 * (int64_t)sgi + 1] = gn;
                 }
             }
+        };
+        // one sum per tile (tensor) of the chunk; usually all of the chunk is one
+        // (a path of its own: the masks of the others cost half as much again)
+        if (s1 - s0 == 1 && len == (int)kTileElems) {
+            tile_sums(std::false_type{}, s0, 0, (int)kTileElems);
+        } else {
+            for (int32_t sgi = s0; sgi < s1; ++sgi) {
+                const Tile t = p.tiles[sgi];
+                tile_sums(std::true_type{}, sgi, (int)(t.start - lo), t.len);
+            }
         }
         if (due) {
+            asm volatile("");   // (a branch, not a select for every element)
 #pragma unroll
             for (int r = 0; r < R; ++r)
                 if (has[r]) x[r] = mean;
@@ -803,7 +844,7 @@ __global__ void __launch_bounds__(64) k_sync_loop(SpanParams p) {
             if (full) { h = ld4<false>(a.h + e0); xs = ld4<false>(a.xs + e0); }
             else { h = ld4_masked(a.h + e0, e0, lo, hi); xs = ld4_masked(a.xs + e0, e0, lo, hi); }
         }
-        const GroupData gd = group_data(a, g, h, xs);
+        const auto gd = group_data<8>(a, g, h, xs);
         f4 s = splat(0.0f), sm = splat(0.0f);
         for (int k = 0; k < a.K; ++k) {
             float *xrow = a.x + (int64_t)k * a.ld + e0;
@@ -1335,19 +1376,24 @@ hipError_t span_variant(const SpanParams &p, bool vec, bool nt, hipStream_t st) 
     });
 }
 
-// A compiled K runs a span in one of two layouts.  One row per wave (two at K =
-// 32) streams best and has the most waves; several rows per wave share the
-// lanes' Philox products and the work of a sync.  Measured for 1 / 2 / 3 / 4 / 8
-// steps with a sync at the end: K = 8, P = 138M 3.09 / 3.13 / 3.32 / 3.63 / 5.45
-// ms with one row, 3.28 / 3.27 / 3.25 / 3.24 / 5.02 with two; K = 16, P = 25.6M
-// 1.12 / 1.14 / 1.27 / 1.39 / 2.06 and 1.20 / 1.20 / 1.21 / 1.20 / 1.83 (four
-// rows).  So from three steps on the taller layout, and at K = 32 always (104
-// against 107 us), unless its waves would not give every SIMD two: 64 steps with
-// 8 syncs at K = 4, P = 65,536 take 19 us in 1024 one-row waves, 29 in 512.
-template <int KT, int WIDE, int TALL>
+// A compiled K runs a span in one of three layouts.  One row per wave (two at K =
+// 32) streams best and has the most waves: one and two steps, bound by HBM (K = 8,
+// P = 11.2M, single steps with their sync 1.08 ms for four against 1.13 with eight
+// rows per wave).  More rows per wave share the lanes' Philox products and the
+// work of a sync, and with all rows in one wave a sync needs no barrier: 32 steps at
+// K = 8, P = 138M 22.3 ms with two rows per wave, 20.6 with eight; 60 steps at K =
+// 4, P = 20M 3.70 (two) and 3.44 (four); 400 at K = 32, P = 1.2M 10.1-11.1 (four)
+// and 9.1 (eight); but 100 at K = 16, P = 25.6M 22.0 (four) and 22.5 (eight; 22.7 in
+// one wave of 16 rows, which leaves two waves a SIMD).  A layout needs two waves
+// for every SIMD: 64 steps with 8 syncs at K = 4, P = 65,536 take 19 us in 1024
+// one-row waves, 29 in 512 of two.
+template <int KT, int WIDE, int MID, int TALL>
 hipError_t span_dispatch(const SpanParams &p, bool vec, bool nt, hipStream_t st) {
-    const bool fills = p.n_chunks * span_waves<KT, TALL>() >= 2 * kSimds;
-    if (fills && (p.when.n >= 3 || KT == 32)) return span_variant<KT, TALL>(p, vec, nt, st);
+    auto fills = [&](int waves) { return p.n_chunks * waves >= 2 * kSimds; };
+    if (p.when.n >= 3 || KT == 32) {
+        if (fills(span_waves<KT, TALL>())) return span_variant<KT, TALL>(p, vec, nt, st);
+        if (fills(span_waves<KT, MID>())) return span_variant<KT, MID>(p, vec, nt, st);
+    }
     return span_variant<KT, WIDE>(p, vec, nt, st);
 }
 
@@ -1450,11 +1496,11 @@ hipError_t launch_span(const SpanParams &p, int64_t n_tiles, bool vec, bool nt, 
     const int K = p.s.K;
     switch (K) {
     case 1: return span_variant<1, 1>(p, vec, nt, st);
-    case 2: return span_dispatch<2, 1, 2>(p, vec, nt, st);
-    case 4: return span_dispatch<4, 1, 2>(p, vec, nt, st);
-    case 8: return span_dispatch<8, 1, 2>(p, vec, nt, st);
-    case 16: return span_dispatch<16, 1, 4>(p, vec, nt, st);
-    case 32: return span_dispatch<32, 2, 4>(p, vec, nt, st);
+    case 2: return span_dispatch<2, 1, 2, 2>(p, vec, nt, st);
+    case 4: return span_dispatch<4, 1, 2, 4>(p, vec, nt, st);
+    case 8: return span_dispatch<8, 1, 2, 8>(p, vec, nt, st);
+    case 16: return span_dispatch<16, 1, 4, 4>(p, vec, nt, st);
+    case 32: return span_dispatch<32, 2, 4, 8>(p, vec, nt, st);
     default: break;
     }
     if (any_k_kernel(K, false)) {

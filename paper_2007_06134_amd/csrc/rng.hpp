@@ -50,6 +50,26 @@ __device__ __forceinline__ u4 philox10(u4 c, const RoundKeys &rk) {
     return c;
 }
 
+// v in a vector register.  An instruction of single-precision arithmetic or a
+// v_bitop3_b32 issues in 2 cycles a wave when all its operands are vector
+// registers or constants, and in 4 with a scalar register among them (measured
+// with eight waves a SIMD: 1.1-1.2 ns against 1.7-1.9), so what the steps of a
+// launch use again and again is kept in vector registers, uniform as it is.
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t v) {
+    uint32_t r;
+    asm("v_mov_b32 %0, %1" : "=v"(r) : "s"(v));
+    return r;
+}
+__device__ __forceinline__ float in_vgpr(float v) { return __uint_as_float(in_vgpr(__float_as_uint(v))); }
+
+// v >> 8 in the three-operand encoding, which issues in 2 cycles; the compiler
+// would take the short one, which issues in 4.
+__device__ __forceinline__ uint32_t shift_right8(uint32_t v) {
+    uint32_t r;
+    asm("v_lshrrev_b32_e64 %0, 8, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+
 // Three-input exclusive or (one v_bitop3_b32).
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
@@ -71,7 +91,24 @@ __device__ __forceinline__ PhiloxGroup philox_group(uint32_t g, const RoundKeys 
     const uint64_t b = (uint64_t)z * 0xCD9E8D57u;
     return PhiloxGroup{(uint32_t)a, (uint32_t)(b >> 32), (uint32_t)b};
 }
-__device__ __forceinline__ u4 philox_noise(const PhiloxGroup &pg, uint32_t k, uint32_t t, const RoundKeys &rk) {
+// The keys of rounds 2 to 9, the first ROUNDS rounds' in vector registers.
+template <int ROUNDS>
+struct NoiseKeys {
+    uint32_t lo[8], hi[8];
+};
+template <int ROUNDS>
+__device__ __forceinline__ NoiseKeys<ROUNDS> noise_keys(const RoundKeys &rk) {
+    NoiseKeys<ROUNDS> nk;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        nk.lo[r] = r < ROUNDS ? in_vgpr(rk.lo[r + 2]) : rk.lo[r + 2];
+        nk.hi[r] = r < ROUNDS ? in_vgpr(rk.hi[r + 2]) : rk.hi[r + 2];
+    }
+    return nk;
+}
+template <int ROUNDS>
+__device__ __forceinline__ u4 philox_noise(const PhiloxGroup &pg, uint32_t k, uint32_t t, const RoundKeys &rk,
+                                           const NoiseKeys<ROUNDS> &nk) {
     const uint64_t pt = (uint64_t)t * 0xCD9E8D57u;                   // scalar: round 0
     const uint32_t x = (uint32_t)(pt >> 32) ^ k ^ rk.lo[0];
     const uint64_t px = (uint64_t)x * 0xD2511F53u;                   // scalar: round 1
@@ -84,8 +121,8 @@ __device__ __forceinline__ u4 philox_noise(const PhiloxGroup &pg, uint32_t k, ui
     for (int r = 2; r < 10; ++r) {
         const uint64_t prod_a = (uint64_t)c.x * 0xD2511F53u;
         const uint64_t prod_b = (uint64_t)c.z * 0xCD9E8D57u;
-        c.x = xor3((uint32_t)(prod_b >> 32), c.y, rk.lo[r]);
-        c.z = xor3((uint32_t)(prod_a >> 32), c.w, rk.hi[r]);
+        c.x = xor3((uint32_t)(prod_b >> 32), c.y, nk.lo[r - 2]);
+        c.z = xor3((uint32_t)(prod_a >> 32), c.w, nk.hi[r - 2]);
         c.y = (uint32_t)prod_b;
         c.w = (uint32_t)prod_a;
     }
@@ -119,12 +156,14 @@ __device__ __forceinline__ f4 normals4(u4 r) {
 // base + sigma z for the two normals z of words a and b, with
 // s = sigma sqrt(2 ln 2): sigma times the radius is s sqrt(-log2 u1), so the
 // noise level and the logarithm's base cost one product for two normals, and
-// the cosine's and the sine's product takes the sum.  (hi24(a) + 1) 2^-24 is
-// exact in the fma.
+// the cosine's and the sine's product takes the sum.  The bits of n = hi24(a) are
+// also the float n 2^-149 (a denormal, or the first normal binade), so the
+// product with 2^125 is n 2^-24 without a conversion, exact, and the fma's sum
+// with 2^-24 is too.
 __device__ __forceinline__ void add_noise2(float s, uint32_t a, uint32_t b, float base0, float base1, float &d0,
                                            float &d1) {
-    const float u1 = fmaf((float)(a >> 8), 0x1p-24f, 0x1p-24f);
-    const float u2 = (float)(b >> 8) * 0x1p-24f;
+    const float u1 = fmaf(__uint_as_float(shift_right8(a)), 0x1p125f, 0x1p-24f);
+    const float u2 = __uint_as_float(shift_right8(b)) * 0x1p125f;
     const float radius = s * __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1));
     d0 = fmaf(radius, __builtin_amdgcn_cosf(u2), base0);
     d1 = fmaf(radius, __builtin_amdgcn_sinf(u2), base1);

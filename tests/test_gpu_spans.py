@@ -60,11 +60,11 @@ def _by_hand(A, w, n, pad=True):
 
 # worker counts of every layout: compiled (one row per wave, and several with
 # enough chunks), K an argument with 1, 2, 4 and 8 rows per wave (whole and
-# ragged last waves), the loop kernel; 140,000 elements give every tall layout
-# two waves per SIMD, 3,000 none
+# ragged last waves), the loop kernel; the larger sizes give the layouts of more
+# rows per wave two waves per SIMD, just, 3,000 elements none
 @pytest.mark.parametrize("avg_m", [False, True])
 @pytest.mark.parametrize("K,P", [(1, 3000), (2, 530_001), (4, 270_001), (8, 140_001), (16, 140_001), (32, 70_001), (8, 3000),
-                                 (32, 3000), (3, 9001), (7, 9001), (24, 9001), (33, 5001), (64, 5001), (65, 3001),
+                                 (32, 3000), (4, 524_289), (8, 524_035), (32, 131_073), (3, 9001), (7, 9001), (24, 9001), (33, 5001), (64, 5001), (65, 3001),
                                  (100, 3001), (128, 3000), (129, 2001)])
 def test_run_equals_one_step_launches(A, K, P, avg_m):
     """A constant-period run (whole spans of syncs) against single-step launches:
