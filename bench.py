@@ -7,11 +7,13 @@ every local step, every fused sync (mean, broadcast, per-tensor variance) and
 every controller decision.  The replicas and momentum buffers are reset to
 zero at the start of each run; h and x* stay resident in HBM.
 
-Metric: parameter-updates/s = K * P * 500 * steps / time.  The roofline entry
-is for the dominant kernel (the plain local step): algorithmic bytes per
-launch (16 K P + 8 P) over its mean duration from HIP events recorded on the
-library's stream during the timed region, around every 8th launch of each
-kernel kind (--timing-every) so that the events barely disturb the job.
+Metric: parameter-updates/s = K * P * 500 * steps / time.  A launch takes
+several steps and their syncs in one pass over x and m, so the roofline entry
+is the issue rate of a step's instructions: K P updates over a step's share of
+its launch (HIP events recorded on the library's stream during the timed
+region, around every 8th launch of each kernel kind, --timing-every, so that
+the events barely disturb the job), against the rate at which eight waves a
+SIMD issue the step alone.
 
 Prints one JSON line.
 """
@@ -28,7 +30,8 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-HBM_PEAK_GBS = 8000.0
+# 256 updates (a wave's step of one worker) on each of 1024 SIMDs every 112 ns
+ISSUE_PEAK = 256 * 1024 / 112e-9
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "local_step_k8_p138m_traffic.md")
 
 
@@ -246,32 +249,30 @@ def main():
         out["config"]["mode"] = "traced"
     if tm.trace_launches > 0:
         trace_ms = tm.trace_ms / tm.trace_launches
-        out["traced_step"] = {"avg_launch_ms": trace_ms, "achieved_GBs": step_bytes / (trace_ms * 1e-3) / 1e9}
+        out["traced_step"] = {"avg_launch_ms": trace_ms}
     if tm.step_launches > 0:
         step_ms = tm.step_ms / tm.step_launches
-        achieved = step_bytes / (step_ms * 1e-3) / 1e9
+        achieved = w.K * w.P / (step_ms * 1e-3)
         traffic = measured_traffic(w, step_block, step_lds, step_row_chunks)
-        out["roofline"] = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                           "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                           # traffic is not measured in this run: it is the copy-scaled
-                           # FETCH_SIZE + WRITE_SIZE of a separate rocprofv3 --pmc run,
-                           # read from the committed summary when it was taken on these
-                           # kernel sources and this launch shape (else null)
+        out["roofline"] = {"bound": "vector issue", "achieved": achieved, "peak": ISSUE_PEAK,
+                           "unit": "param-updates/s", "frac": achieved / ISSUE_PEAK, "traffic": traffic,
+                           # traffic (of a launch of one local step) is not measured in this
+                           # run: it is the copy-scaled FETCH_SIZE + WRITE_SIZE of a separate
+                           # rocprofv3 --pmc run, read from the committed summary when it was
+                           # taken on these kernel sources and this launch shape (else null)
                            "traffic_source": {"profile": os.path.relpath(TRAFFIC_FILE, ROOT),
                                               "kernel_sources_digest": kernel_source_digest(),
                                               "matched": traffic is not None},
-                           "kernel": f"k_local_step<{step_block}>",
-                           "lds_reserved_per_block": step_lds, "row_chunks": step_row_chunks,
-                           "row_stride": row_stride,
-                           "bytes_per_launch": step_bytes,
+                           "kernel": "k_span",
+                           "local_step_block": step_block, "lds_reserved_per_block": step_lds,
+                           "row_chunks": step_row_chunks, "row_stride": row_stride,
+                           "bytes_per_pass": step_bytes,
                            "avg_launch_ms": step_ms, "timed_launches": tm.step_launches,
                            "timed_every": args.timing_every}
         if tm.fused_launches > 0:
             fused_ms = tm.fused_ms / tm.fused_launches
             out["fused_step_sync"] = {"avg_launch_ms": fused_ms,
-                                      "achieved_GBs": step_bytes / (fused_ms * 1e-3) / 1e9,
                                       "segsum_avg_ms": tm.segsum_ms / max(tm.segsum_launches, 1)}
-        out["hbm_GBs_whole_run"] = (step_bytes * N * args.steps) / elapsed / 1e9
     if sep:
         out["separate_sync"] = sep
     if not args.no_timing:
