@@ -1197,10 +1197,10 @@ __global__ void __launch_bounds__(kFinishThreads) k_reduce_finish(ReduceParams r
             r.sums[2 * slot] = tot.a;
             r.sums[2 * slot + 1] = tot.b;
         } else {
-            const int64_t t = sp.t + j;
-            const int32_t p_t = period_at(r.rule, r.st0.p, t);
-            write_hdr(slot_hdr(r, slot), t, sp.n, due, p_t, p_t,
-                      __builtin_isfinite(tot.a) ? ADPSGD_OK : ADPSGD_ENONFINITE, tot.a, tot.b, r.st0.C2, r.st0.nC2);
+            // (no p, C2 or nC2: they are the host's alone here, and a captured launch
+            // serves runs from states that differ in them)
+            write_hdr(slot_hdr(r, slot), sp.t + j, sp.n, due, 0, 0,
+                      __builtin_isfinite(tot.a) ? ADPSGD_OK : ADPSGD_ENONFINITE, tot.a, tot.b, 0.0, 0);
         }
     }
 }

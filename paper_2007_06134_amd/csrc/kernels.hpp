@@ -153,8 +153,8 @@ constexpr int kAverageCapWaves = 24;
 struct SlotHdr {
     int64_t t;        // the measured step (the launch's last without a measurement)
     int32_t due;      // 1: a sync followed the step
-    int32_t p;        // period in force for the step
-    int32_t p_next;   // period after the sync's decision
+    int32_t p;        // period in force for the step (p, p_next, C2 and nC2: with the controller
+    int32_t p_next;   // on the device, else 0), and after the sync's decision
     int32_t status;   // ADPSGD_OK, or ADPSGD_ENONFINITE when S was not finite
     double S;         // sum over tensors of the variances (0 without a measurement)
     double GN;        // sum over tensors of the gradient norms^2
@@ -193,7 +193,7 @@ struct ReduceParams {
     int32_t slot0, ring;
     SchedState *sched;            // the controller state (when.device or control)
     int32_t control;              // 1: decisions are taken here and the state is kept up
-    SchedState st0;               // control = 0: the state for the records (no sync moves it)
+    int32_t pad_;
     SchedRule rule;
     SpanWhen when;                // as in the launch that is reduced
     double gamma[kSpanSteps];     // rates in fp64 (Algorithm 2's gamma_t) from step when.t on

@@ -511,7 +511,7 @@ ReduceParams reduce_params(const adpsgd_ctx *c, const SpanWhen &w, char *recs, i
     r.ring = ring;
     r.sched = c->d_sched;
     r.control = control ? 1 : 0;
-    r.st0 = SchedState{c->st.t, c->st.cnt, c->st.nC2, c->st.C2, c->st.p, 0};
+    r.pad_ = 0;
     r.rule = rule_of(&c->hp);
     r.when = w;
     for (int32_t j = 0; j < n_rates(w); ++j) r.gamma[j] = adpsgd_lr(&c->hp, w.t + j);
@@ -1082,7 +1082,8 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
         ++n_done;
         // (a non-finite S still restarted the counter; only p and C2 stay)
         if (rc) return hdr.status == rc ? rc : fail(ADPSGD_ESTATE, "device and host disagree on a non-finite S");
-        if (hdr.status != ADPSGD_OK || hdr.p_next != known.p || hdr.C2 != known.C2 || hdr.nC2 != known.nC2)
+        if (hdr.status != ADPSGD_OK ||
+            (control && (hdr.p_next != known.p || hdr.C2 != known.C2 || hdr.nC2 != known.nC2)))
             return fail(ADPSGD_ESTATE, "device and host controllers disagree at step " + std::to_string(t));
         return ADPSGD_OK;
     };

@@ -404,6 +404,33 @@ def test_graph_replays_equal_eager_runs(A, key):
     assert max_rel_err(x, r.x, w.offsets()) < PARAM_TOL
 
 
+@pytest.mark.parametrize("mode", [W.PERIOD_CONST, W.PERIOD_ALG1])
+def test_graph_replays_serve_states_of_another_c2(A, mode):
+    """A constant-period run does not touch C2 and nC2, so a captured run serves
+    every state that differs from the captured one in them alone: restored states
+    and a reset after one, against the host-waiting policy (never captured)."""
+    w = _tiny(K=4, sizes=(3000, 77), period_mode=mode, p_init=3, total_steps=40)
+    with A.Adpsgd.from_workload(w) as a, A.Adpsgd.from_workload(w) as b:
+        b.set_launch_policy(A.LAUNCH_HOST)
+        for C2, nC2 in ((0.0, 0), (0.25, 3), (1e-300, 1), (-7.5, 0), (0.0, 2), (None, None)):
+            recs = []
+            for eng in (a, b):
+                eng.reset()
+                if C2 is not None:
+                    st = eng.get_state()
+                    st.C2, st.nC2 = C2, nC2
+                    eng.set_state(st)
+                r, var, _ = eng.run(25)
+                assert all(r["C2"] == (C2 or 0.0))
+                st = eng.get_state()
+                recs.append((r.tobytes(), var.tobytes(), eng.x.cpu().numpy().tobytes(),
+                             (st.t, st.cnt, st.p, st.C2, st.nC2)))
+            assert recs[0] == recs[1]
+            assert recs[0][3][3:] == (C2 or 0.0, nC2 or 0)
+        tm = a.get_timing()
+        assert (tm.graph_captures, tm.graph_replays) == (1, 6)
+
+
 @pytest.mark.parametrize("key,fused", [("resnet18_like", True), ("many_small", True),
                                        ("quad_small", True), ("resnet18_like", False)])
 def test_manual_algorithm2_loop_equals_run(A, key, fused):
