@@ -101,6 +101,54 @@ def test_local_steps_match_oracle(A, K, sizes):
     assert max_rel_err(m, r.v, w.offsets(), floor=MOM_FLOOR) < MOM_TOL
 
 
+# Curvatures around and far below the weight decay, and values only a caller's own h
+# holds (h = 0, equal to the decay and one bit to either side, negative).
+def _curvatures(kind, wd, n):
+    if kind == "special":
+        w32 = np.float32(wd)
+        return np.resize(np.array([0.0, w32, np.nextafter(w32, np.float32(0)), np.nextafter(w32, np.float32(9)), -w32 / 2,
+                                   w32 * 2.0**-30, w32 * 8, -w32], dtype=np.float32), n)
+    lo, hi = kind
+    return np.exp(np.random.default_rng(4).uniform(np.log(lo), np.log(hi), n)).astype(np.float32)
+
+
+# sigma = 0: fp32 arithmetic emulated with h (x - x*) + wd x leaves x within 1.0e-6 in this
+# metric over these rows; the bar is four times that.  (h + wd) (x - x*) + wd x* cancels
+# where wd > h and is 4.5e-5 to 1.0e-3 off.
+DECAY_TOL = 4e-6
+
+
+@pytest.mark.parametrize("wd,h", [(5e-4, (1e-6, 1e-4)), (1.0, (1e-3, 1e-2)), (1.0, (1e-3, 1e-3)), (0.1, (1e-5, 1e-5)),
+                                  (0.1, (0.05, 0.2)), (0.25, "special"), (0.0, (1e-2, 1.0))])
+@pytest.mark.parametrize("K", [4, 5, 129])
+def test_weight_decay_above_the_curvature_matches_oracle(A, K, wd, h):
+    import torch
+    w = _tiny(K=K, sizes=(3000, 5, 1091), sigma=0.0, weight_decay=wd, p_init=10**6 if K == 129 else 4,
+              total_steps=200)
+    off = w.offsets()
+    h32 = _curvatures(h, wd, w.P)
+    # (no syncs at K = 129: its mean adds the rows in order, so that of equal rows is up to
+    # 128 2^-24 = 7.6e-6 of itself off at each of 50 syncs, whatever the steps' form)
+    for call in ("local_steps", "traced") if K == 129 else ("local_steps", "run", "traced"):
+        n = 30 if call == "traced" else 200
+        with A.Adpsgd.from_workload(w) as eng:
+            eng.h.copy_(torch.from_numpy(h32))
+            xs = eng.xstar.double().cpu().numpy()
+            if call == "local_steps":
+                eng.local_steps(n)
+            elif call == "run":
+                eng.run(n)
+            else:
+                steps = eng.run_traced(n)[3]
+            x = eng.x.double().cpu().numpy()
+        r = oracle.Oracle(w).run(n_steps=n, h=h32.astype(np.float64), xs=xs, trace=call == "traced")
+        err = max_rel_err(x, r.x, off)
+        _say(f"wd {wd} h {h} K {K} {call}: x {err:.1e}")
+        assert err < DECAY_TOL
+        if call == "traced":   # (before the gradient has vanished)
+            assert rel_err(steps["grad_norm2"], r.trace_grad_norm2) < 1e-5
+
+
 # K = 12, 24: the sync-tile kernel with K as an argument (two rows per wave);
 # 25: the same with a ragged last wave; 33, 48, 64: four rows per wave (33
 # ragged); 3: the loop kernel for the separate sync (one row per wave when a
