@@ -20,6 +20,7 @@
 
 #include "adpsgd.h"
 #include "common.hpp"
+#include "driver.hpp"
 #include "kernels.hpp"
 
 namespace adpsgd {
@@ -72,10 +73,6 @@ constexpr int kTimedMax = 4096;    // pending timed launches before a harvest
 constexpr int32_t kSpanSlots = 16;
 constexpr int64_t kSpanSlotBytes = int64_t(64) << 20;
 constexpr int64_t kMaxInflight = 64;   // launches the host has not yet accounted for
-// Launches in flight whose end only the device knows, at most: with one queued
-// behind the one that runs, the GPU does not wait for the host to read a record;
-// more keep it busy where a launch is shorter than that takes.
-constexpr int kMaxOpen = 3;
 // Between waits, the driver polls for finished records every kPollEvery launches
 // (each poll is a runtime call; steps without a record need no accounting to proceed).
 constexpr int64_t kPollEvery = 8;
@@ -448,16 +445,6 @@ SyncParams sync_params(const adpsgd_ctx *c) {
     return sp;
 }
 
-// A span the host planned: steps t .. t + n - 1, bit j of syncs set when a sync
-// follows step t + j; measure: every step is measured.
-SpanWhen planned(int64_t t, int32_t n, uint64_t syncs, bool measure) {
-    return SpanWhen{t, t + n, syncs, n, 0, 1, measure ? 1 : 0, 0, 0};
-}
-int measurements(const SpanWhen &w) {
-    if (w.measure) return w.n;
-    return w.device ? 1 : __builtin_popcountll(w.syncs);
-}
-
 // Rates from step w.t on: a launch with an unknown first step may begin up to
 // kSpanSteps - 1 steps later.
 int32_t n_rates(const SpanWhen &w) { return w.device && !w.known ? kSpanSteps : w.n; }
@@ -548,54 +535,9 @@ int enqueue_span(adpsgd_ctx *c, const SpanWhen &w, int slot0, bool control, int6
     return ok();
 }
 
-// Step st->t of a known schedule: true if a sync follows it (the counter then
-// restarts; p stays, whatever the sync decides).
-bool plan_step(const SchedRule &rule, adpsgd_state *st) {
-    const int64_t t = st->t++;
-    st->cnt += 1;
-    st->p = period_at(rule, st->p, t);
-    const bool due = sync_due(rule, st->cnt, st->p, t);
-    if (due) st->cnt = 0;
-    return due;
-}
-
-// The next launch of a schedule known from state st on: steps up to `most` and
-// `end`, ending after the last sync that fits n_slots (every step needs a slot
-// when all are measured), after a sync whose outcome may move p, or at the end.
-// Without measurements it is plain steps.  st is moved to the state after it.
-// merge: launches of the run leave merged rows at syncs; merged: one did.
-SpanWhen plan_span(const adpsgd_ctx *c, adpsgd_state *st, int64_t end, bool measure, bool merge, bool merged) {
-    const SchedRule rule = rule_of(&c->hp);
-    SpanWhen w = planned(st->t, 0, 0, measure);
-    w.end = end;
-    w.merge = merge ? 1 : 0;
-    w.merged = merged ? 1 : 0;
-    int slots = 0;
-    adpsgd_state after_sync = *st;   // the state after the last sync of the span
-    int32_t n_sync = 0;
-    while (w.n < kSpanSteps && st->t < end && slots < c->n_slots) {
-        const int64_t t = st->t;
-        const bool due = plan_step(rule, st);
-        if (due) w.syncs |= uint64_t(1) << w.n;
-        ++w.n;
-        if (due || measure) ++slots;
-        if (due) {
-            after_sync = *st;
-            n_sync = w.n;
-        }
-        if (due && sync_decisive(rule, t)) break;
-    }
-    // the steps after the last sync go with the next launch, which measures them
-    // too, unless the run ends here
-    if (n_sync > 0 && st->t < end && !measure) {
-        *st = after_sync;
-        w.n = n_sync;
-    }
-    return w;
-}
-
-// Capture the spans of a schedule that no decision moves as a graph: the spans, and after each the reduction into as many of the graph's record slots.
-// No events: records are read after the whole graph has run.
+// Capture the spans of a schedule that no decision moves as a graph: the spans, and
+// after each the reduction into as many of the graph's record slots.  No events:
+// records are read after the whole graph has run.
 int capture_run(adpsgd_ctx *c, const std::vector<SpanWhen> &spans, int64_t n_sync) {
     drop_graph(c);
     if (n_sync > c->gslot_cap) {
@@ -1044,6 +986,8 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
     const bool control = adaptive || by_step;   // the controller state lives on the device
     const bool merge = !by_step && c->K > 1 && span_in_registers(c->K);
     const int64_t t0 = c->st.t, end = t0 + n_steps;
+    const Planner planner{rule, end, c->n_slots, traced, by_step, c->policy == ADPSGD_LAUNCH_HOST,
+                          span_in_registers(c->K), merge};
 
     // A run whose schedule is fixed in advance (constant-period modes) on a
     // small, launch-bound problem replays a captured graph of the whole run.
@@ -1128,7 +1072,7 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
         adpsgd_state pl = known;
         int64_t n_sync = 0;
         while (pl.t < end) {
-            spans.push_back(plan_span(c, &pl, end, false, merge, merge && !spans.empty() && pl.cnt == 0));
+            spans.push_back(planner.span(&pl, merge && !spans.empty() && pl.cnt == 0));
             n_sync += measurements(spans.back());
         }
         const int64_t key[7] = {t0, n_steps, known.cnt, known.p, c->step_shape.block, c->step_shape.lds,
@@ -1188,28 +1132,7 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
         return ADPSGD_OK;
     };
 
-    // The schedule after every launch in flight, as far as the host knows it: st
-    // exactly; exactly but for p, which a decision in flight may move by one
-    // (p_open); or only that the next step lies in [st.t, t_hi], behind n_open
-    // launches that the device ends after decisions in flight.
-    struct Ahead { adpsgd_state st; int64_t t_hi; bool p_open; int n_open; };
-    auto pass = [&](Ahead *a, const SpanWhen &w) {
-        if (by_step) {
-            a->t_hi = ++a->st.t;
-        } else if (w.device && (a->p_open || a->n_open > 0)) {
-            a->n_open += 1;
-            a->t_hi = std::min(end, a->t_hi + w.n);
-        } else {
-            for (int32_t j = 0; j < w.n && a->st.t < end; ++j) {
-                const int64_t t = a->st.t;
-                const bool due = plan_step(rule, &a->st);
-                a->p_open = a->p_open || (due && sync_decisive(rule, t));
-                if (due && w.device) break;
-            }
-            a->t_hi = a->st.t;
-        }
-    };
-    Ahead ahead{known, known.t, false, 0};
+    Planner::Ahead ahead = Planner::known(known);   // after every launch in flight
 
     int hard = ADPSGD_OK;  // a HIP failure: stop at once
     while (hard == ADPSGD_OK) {
@@ -1218,11 +1141,10 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
             if (c->timing && (hard = harvest(c, false))) break;
         }
         if (dirty) {
-            ahead = Ahead{known, known.t, false, 0};
-            for (const Entry &e : inflight) pass(&ahead, e.w);
+            ahead = Planner::known(known);
+            for (const Entry &e : inflight) planner.pass(&ahead, e.w);
             dirty = false;
         }
-        const adpsgd_state &pl = ahead.st;
         if (status != ADPSGD_OK || ahead.t_hi >= end) {
             // (launches the device ends may stop short of the end: then there is more to do)
             if (inflight.empty()) break;
@@ -1231,33 +1153,7 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
         }
 
         Entry e{SpanWhen{}, -1, 0, -1};
-        bool wait = false;
-        if (by_step) {
-            // one step at a time, decided by the device
-            e.w = SpanWhen{pl.t, end, 0, 1, 1, 1, traced ? 1 : 0, 0, 0};
-        } else if (!ahead.p_open && ahead.n_open == 0) {
-            adpsgd_state to = pl;
-            // (at the start of a run the rows are the caller's)
-            e.w = plan_span(c, &to, end, traced, merge, merge && n_launches > 0 && pl.cnt == 0);
-        } else if (c->policy == ADPSGD_LAUNCH_HOST || ahead.n_open >= kMaxOpen) {
-            wait = true;
-        } else {
-            // a span the device ends, of at most as many steps as the longest
-            // period that the decisions in flight allow
-            const bool at_t = ahead.n_open == 0;
-            const int64_t p_hi = std::min<int64_t>(rule.p_max, (int64_t)pl.p + 1 + ahead.n_open);
-            int64_t most = std::max<int64_t>(1, p_hi - (at_t ? pl.cnt : 0));
-            most = std::min(most, end - pl.t);
-            if (traced) most = std::min<int64_t>(most, c->n_slots);
-            if (!span_in_registers(c->K)) {
-                most = 1;
-                wait = !at_t;
-            }
-            if (at_t) most = std::min<int64_t>(most, kSpanSteps);
-            else if (ahead.t_hi - pl.t + most > kSpanSteps) wait = true;   // the rates it may need do not fit
-            e.w = SpanWhen{pl.t, end, 0, (int32_t)std::min<int64_t>(most, kSpanSteps), 1, at_t ? 1 : 0, traced ? 1 : 0,
-                           merge ? 1 : 0, 0};
-        }
+        bool wait = !planner.next(ahead, n_launches == 0, &e.w);
         if (!wait) {
             e.n_slots = measurements(e.w);
             wait = slots_used + e.n_slots > kRing || (int64_t)inflight.size() >= kMaxInflight;
@@ -1279,7 +1175,7 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
         }
         if (hard) break;
         inflight.push_back(e);
-        pass(&ahead, e.w);
+        planner.pass(&ahead, e.w);
         ++n_launches;
     }
     // whatever was enqueued runs to completion and is accounted for
