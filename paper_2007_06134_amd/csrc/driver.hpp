@@ -125,6 +125,15 @@ struct Planner {
             *w = span(&to, merge && !first && pl.cnt == 0);
             return true;
         }
+        // With too many workers for one launch of a period the device decides a step at a
+        // time, each a launch with a reduction, and ends no period early.  With p > 2 at
+        // least one step is plain whatever the decision in flight says: read its record,
+        // and the whole period goes out as one launch of plain steps and one with its
+        // sync.  160 adaptive steps, p = 4, with one device-decided step and then a wait
+        // / so: 12.8 / 9.1 ms at K = 200, P = 20,000, 13.6 / 9.9 at K = 150, P = 100,000;
+        // with the plain steps queued ahead of the record, in a launch of their own, 9.2
+        // and 11.2.  With p of 1 or 2 the device decides: there is little to gain by waiting.
+        if (!in_registers && !measure && a.n_open == 0 && pl.p > 2) return false;
         if (host_waits || a.n_open >= kMaxOpen) return false;
         // a span the device ends, of at most as many steps as the longest period
         // that the decisions in flight allow

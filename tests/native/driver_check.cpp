@@ -199,7 +199,35 @@ static int run_case(const adpsgd_hparams &hp, const std::vector<int64_t> &cuts, 
     return 0;
 }
 
+// Behind a decision in flight a K of the loop kernel (above 128) reads the record
+// rather than have the device decide a step, unless p is 1 or 2; the period then is
+// one launch.
+static int check_launches_of_many_workers() {
+    g_case = -1;
+    adpsgd_hparams hp{};
+    hp.sigma = 0.1; hp.h_lo = 0.1; hp.h_hi = 1.0; hp.lr0 = 0.1; hp.total_steps = 1000; hp.thr_lo = 0.7; hp.thr_hi = 1.3;
+    hp.period_mode = ADPSGD_PERIOD_ADAPTIVE;
+    hp.p_init = 1;
+    for (int32_t p : {1, 2, 3, 4, 9, 64})
+        for (int policy : {ADPSGD_LAUNCH_HYBRID, ADPSGD_LAUNCH_HOST}) {
+            Planner pl{rule_of(&hp), 1000, 16, false, false, policy == ADPSGD_LAUNCH_HOST, false, false};
+            adpsgd_state st{};
+            st.t = 500;
+            st.p = p;
+            Planner::Ahead a = Planner::known(st);
+            SpanWhen w;
+            CHECK(pl.next(a, false, &w) && !w.device && w.n == p && w.syncs == uint64_t(1) << (p - 1), "p %d", p);
+            pl.pass(&a, w);
+            CHECK(a.p_open && a.st.t == 500 + p && a.st.cnt == 0, "p %d", p);
+            const bool more = pl.next(a, false, &w);
+            CHECK(more == (p <= 2 && policy == ADPSGD_LAUNCH_HYBRID), "p %d", p);
+            CHECK(!more || (w.device && w.known && w.n == 1 && w.t == 500 + p), "p %d", p);
+        }
+    return 0;
+}
+
 int main() {
+    if (check_launches_of_many_workers()) return 1;
     std::mt19937_64 rng(11);
     auto pick = [&](int64_t lo, int64_t hi) { return lo + (int64_t)(rng() % (uint64_t)(hi - lo + 1)); };
     Counts n{};

@@ -96,7 +96,7 @@ def test_unaligned_and_cut_rows(A, K, pad):
 # steps one at a time where the device decides
 @pytest.mark.parametrize("traced", [False, True])
 @pytest.mark.parametrize("K,p,N", [(4, 1, 90), (4, 15, 120), (8, 17, 150), (4, 63, 300), (8, 64, 300), (4, 66, 340),
-                                   (8, 130, 500), (129, 3, 40)])
+                                   (8, 130, 500), (129, 3, 40), (129, 1, 40), (200, 9, 90), (160, 70, 300)])
 def test_adaptive_periods_agree_under_every_policy(A, K, p, N, traced):
     """Adaptive runs whose period moves (a decisive sync from the second on): the
     default driver's spans, single device-decided steps and host-planned
