@@ -320,9 +320,9 @@ ADPSGD_API int adpsgd_get_step_launch(const adpsgd_ctx *c, int32_t *block, int32
 ADPSGD_API int adpsgd_set_launch_policy(adpsgd_ctx *c, int32_t policy);
 
 /* Per-kernel HIP-event timing (off by default).  every = 0: off; every >= 1:
- * HIP events around every every-th launch of each kernel kind (1: all), so the
- * events disturb the timed work little; adpsgd_timing then holds the sampled
- * launches.  Setting or reading it waits for the stream; setting it clears the
+ * HIP events around the first and then every every-th launch of each kernel kind
+ * (1: all; a launch of several steps counts as that many), so the events disturb
+ * the timed work little; adpsgd_timing then holds the sampled launches.  Setting or reading it waits for the stream; setting it clears the
  * totals.  EINVAL for every < 0. */
 ADPSGD_API int adpsgd_set_timing(adpsgd_ctx *c, int32_t every);
 ADPSGD_API int adpsgd_get_timing(adpsgd_ctx *c, adpsgd_timing *out);

@@ -349,9 +349,10 @@ int harvest(adpsgd_ctx *c, bool wait_all) {
 }
 
 // Launch, with HIP events around it when timing is on and this launch is
-// sampled: a launch of `steps` steps counts as that many of its class, and is
-// timed when no more than one in timing_every of the class (rounded up) is
-// timed with it.  kind -1: a span, described later (set_timed_span).  *seq (may
+// sampled: a launch of `steps` steps counts as that many of its class.  The first
+// launch of a class is timed (work of fewer than timing_every launches' steps
+// would go unseen otherwise), then one with which no more than one in
+// timing_every of the class (rounded up) is timed.  kind -1: a span, described later (set_span).  *seq (may
 // be null) receives the launch's sequence number, or -1 when it is not timed.
 template <class F>
 int timed_launch(adpsgd_ctx *c, int kind, F launch, int64_t *seq = nullptr, int32_t steps = 1) {
@@ -360,7 +361,8 @@ int timed_launch(adpsgd_ctx *c, int kind, F launch, int64_t *seq = nullptr, int3
     bool sampled = false;
     if (c->timing) {
         c->class_seen[cls] += steps;
-        sampled = (c->class_timed[cls] + steps) * c->timing_every <= c->class_seen[cls] + c->timing_every - 1;
+        sampled = c->class_timed[cls] == 0 ||
+                  (c->class_timed[cls] + steps) * c->timing_every <= c->class_seen[cls] + c->timing_every - 1;
     }
     if (!sampled) {
         HIP_TRY(launch());
@@ -388,13 +390,13 @@ int timed_launch(adpsgd_ctx *c, int kind, F launch, int64_t *seq = nullptr, int3
     return ok();
 }
 
-// Span seq took n steps, `syncs` of them with a sync and the others of `kind`.
-void set_timed_span(adpsgd_ctx *c, int64_t seq, int kind, int32_t n, int32_t syncs) {
+// A span of at most `most` steps (timed under sequence number seq, or not) took n,
+// `syncs` of them with a sync and the others of `kind`.
+void set_span(adpsgd_ctx *c, int64_t seq, int32_t most, int kind, int32_t n, int32_t syncs) {
+    if (c->timing) c->class_seen[cSpan] += n - most;   // (the sampling counted the most)
     const int64_t i = seq - c->timed_popped;
     if (seq < 0 || i < 0 || i >= (int64_t)c->timed.size()) return;
     TimedLaunch &tl = c->timed[(size_t)i];
-    // (the sampling counted the most steps the span could take)
-    c->class_seen[cSpan] += n - tl.steps;
     c->class_timed[cSpan] += n - tl.steps;
     tl.kind = kind;
     tl.steps = n;
@@ -1062,7 +1064,7 @@ static int run_impl(adpsgd_ctx *c, int64_t n_steps, adpsgd_sync_rec *log, int64_
             const int rc = account_slot(slot++, t, due != 0);
             if (rc && !first) first = rc;
         }
-        set_timed_span(c, e.seq, traced ? tTrace : tStep, n, n_sync);
+        set_span(c, e.seq, e.w.n, traced ? tTrace : tStep, n, n_sync);
         return first;
     };
 

@@ -747,6 +747,30 @@ def test_timing_counts_every_launch(A):
     assert abs(ts.step_ms / ts.step_launches - tm.step_ms / tm.step_launches) < 0.5 * tm.step_ms / tm.step_launches
 
 
+def test_sampled_timing_sees_short_work(A):
+    """The first launch of each kind is timed, so that work of fewer steps than a
+    sample stands for has a time; more of the same kind adds samples, to one in `every`."""
+    w = _tiny(K=4, sizes=(5000, 77), p_init=4, total_steps=4000)
+    with A.Adpsgd.from_workload(w) as eng:
+        eng.set_timing(8)
+        eng.local_steps(20)
+        eng.average()
+        tm = eng.get_timing()
+        assert tm.step_launches == 20 and tm.step_ms > 0
+        assert tm.average_launches == 1 and tm.segsum_launches == 1 and tm.fused_launches == 0
+        for _ in range(60):
+            eng.local_steps(20)
+        assert 61 * 20 // 8 - 20 <= eng.get_timing().step_launches <= 61 * 20 // 8 + 20
+        eng.set_timing(8)
+        _, _, n = eng.run(24)
+        tm = eng.get_timing()
+        assert n == 6 and tm.fused_launches > 0 and tm.fused_ms > 0 and tm.segsum_launches > 0
+        eng.set_timing(8)
+        eng.step_average()
+        tm = eng.get_timing()
+        assert tm.fused_launches == 1 and tm.fused_ms > 0
+
+
 # ---------------------------------------------------------------- edge cases and errors
 
 def test_maximum_worker_count(A):
