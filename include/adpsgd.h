@@ -357,7 +357,10 @@ ADPSGD_API const char *adpsgd_last_error(void);
 ADPSGD_API int adpsgd_average_noalloc(int32_t K, int64_t P, int64_t row_stride, const int64_t *tensor_offsets,
                                       int32_t T, float *x, double *var_out, void *stream);
 
-/* ---- generator dumps (the device code the steps use) ------------------------ */
+/* ---- generator dumps ---------------------------------------------------------- */
+
+/* c3 = 0 (the noise) runs the device code of the steps, any other tag that of the
+ * problem data (h and x*); the words are the same function of the counter. */
 
 /* dev_out[4j .. 4j+3] = Philox4x32-10(key = (seed mod 2^32, seed >> 32),
  * counter = (g0 + j, c1, c2, c3)) for j < n_groups; device uint32 [4 n_groups].

@@ -1284,20 +1284,27 @@ __global__ void __launch_bounds__(kBlock) k_spread_row(float *a, int64_t ld, int
     else st4_masked(row, ld4_masked(a + e0, e0, 0, P), e0, 0, P);
 }
 
+// The words of counter (g, c1, c2, c3) as the kernels form them: the noise's (tag 0)
+// as a step does, those of the problem data (and of any other tag) as k_init_problem.
+__device__ __forceinline__ u4 dump_words(const RoundKeys &rk, uint32_t g, uint32_t c1, uint32_t c2, uint32_t c3) {
+    if (c3 == TAG_NOISE) return philox_noise(philox_group(g, rk), c1, c2, rk, noise_keys<8>(rk));
+    return philox10(u4{g, c1, c2, c3}, rk);
+}
+
 __global__ void __launch_bounds__(kBlock) k_philox_dump(RoundKeys rk, uint32_t c1, uint32_t c2, uint32_t c3,
                                                         int64_t g0, int64_t n, uint32_t *out) {
     const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (j >= n) return;
-    const u4 r = philox10(u4{(uint32_t)(g0 + j), c1, c2, c3}, rk);
-    *reinterpret_cast<u4 *>(out + 4 * j) = r;
+    *reinterpret_cast<u4 *>(out + 4 * j) = dump_words(rk, (uint32_t)(g0 + j), c1, c2, c3);
 }
 
 __global__ void __launch_bounds__(kBlock) k_normal_dump(RoundKeys rk, uint32_t c1, uint32_t c2, uint32_t c3,
                                                         int64_t g0, int64_t n, float *out) {
     const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (j >= n) return;
-    const f4 z = normals4(philox10(u4{(uint32_t)(g0 + j), c1, c2, c3}, rk));
-    *reinterpret_cast<f4 *>(out + 4 * j) = z;
+    const u4 r = dump_words(rk, (uint32_t)(g0 + j), c1, c2, c3);
+    constexpr float kSqrt2Ln2 = 1.17741002251547469101f;   // a step's scale with sigma = 1
+    *reinterpret_cast<f4 *>(out + 4 * j) = c3 == TAG_NOISE ? add_noise4(kSqrt2Ln2, r, splat(0.0f)) : normals4(r);
 }
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }

@@ -69,6 +69,26 @@ def test_normals_match_oracle(A):
     assert err.max() < 2e-6, err.max()
 
 
+# tag 0: the words and normals as a step forms them (the rounds that depend on the group
+# alone taken out); any other tag: as the problem data's
+@pytest.mark.parametrize("c3", [0, 2, 2**32 - 1])
+@pytest.mark.parametrize("seed,k,t,g0", [
+    (0, 0, 0, 0), (5, 65535, 2**32 - 1, 2**32 - 1000), (2**64 - 1, 7, 2**31, 2**31 - 500), ((3 << 32) | 1, 127, 64, 999),
+])
+def test_noise_of_the_steps_at_counter_edges(A, seed, k, t, g0, c3):
+    import torch
+    n = 1000
+    words = torch.zeros(4 * n, dtype=torch.int32, device="cuda")
+    z = torch.zeros(4 * n, dtype=torch.float32, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    A.adpsgd_philox_dump(seed, k, t, c3, g0, n, words.data_ptr(), st)
+    A.adpsgd_normal_dump(seed, k, t, c3, g0, n, z.data_ptr(), st)
+    torch.cuda.synchronize()
+    assert np.array_equal(words.cpu().numpy().view(np.uint32).reshape(n, 4), oracle.philox_groups(seed, k, t, c3, g0, n))
+    want = oracle.normals_groups(seed, k, t, c3, g0, n).reshape(-1)
+    assert np.max(np.abs(z.cpu().numpy() - want) / np.maximum(1.0, np.abs(want))) < 2e-6
+
+
 @pytest.mark.parametrize("P", [1, 5, 4096, 10_001])
 def test_problem_data_matches_oracle(A, P):
     w = _tiny(K=2, sizes=(P,), h_lo=1e-3)
