@@ -143,6 +143,25 @@ def test_rows_are_whole_between_runs(A, K, mode, pol, avg_m):
             b.x[K - 1].add_(0.01 * (i + 1))
 
 
+# periods longer than a launch: one that begins with merged rows and holds no sync, so
+# that its waves part ways only at a barrier of its own; blocks of one, several and
+# sixteen waves, compiled K and K an argument
+@pytest.mark.parametrize("avg_m", [False, True])
+@pytest.mark.parametrize("mode", [W.PERIOD_CONST, W.PERIOD_ADAPTIVE])
+@pytest.mark.parametrize("K,P", [(2, 3000), (4, 3507), (8, 3507), (8, 600_000), (16, 3507), (16, 140_001), (32, 3507),
+                                 (5, 3507), (3, 3507), (100, 2001)])
+def test_merged_rows_without_a_sync_in_the_launch(A, K, P, mode, avg_m):
+    w = _w(K=K, sizes=(700, 3, P - 703), p_init=130, total_steps=300, avg_momentum=avg_m, period_mode=mode, k_s=100)
+    n = 290                                    # two syncs, at 129 and about 259
+    x, m, syncs, var = _by_hand(A, w, n)
+    assert len(syncs) == 2
+    with A.Adpsgd.from_workload(w) as eng:
+        recs, v, _ = eng.run(n)
+        assert list(recs["t"]) == syncs
+        assert np.array_equal(eng.x.cpu().numpy(), x) and np.array_equal(eng.m.cpu().numpy(), m)
+    assert np.allclose(v, var, rtol=1e-12, atol=0.0)
+
+
 def test_rows_are_whole_after_a_failed_sync(A):
     """A run that a non-finite S stops behind a sync leaves whole rows."""
     w = _w(K=4, sizes=(3000, 5), lr_kind=W.LR_CONST, lr0=50.0, p_init=2, total_steps=300, period_mode=W.PERIOD_ADAPTIVE)
