@@ -599,10 +599,16 @@ __device__ __forceinline__ double tree_sum_lds_d(const double (*rows)[64], int l
     }
 }
 
-// Waves per block of k_span with R rows per wave (K an argument: at most 16).
-template <int KT, int R>
+// With K an argument a block has up to 16 waves.  A CU deals a block's waves out to
+// its four SIMDs, the first getting one more where they do not divide, so it holds
+// two blocks of up to 12 waves when six waves' registers fit a SIMD (FEW), and two
+// of 13 to 16 only when eight's do.
+constexpr int kFewWaves = 12;
+
+// Waves per block of k_span with R rows per wave, at most.
+template <int KT, int R, bool FEW>
 constexpr int span_waves() {
-    if constexpr (KT == 0) return 16;
+    if constexpr (KT == 0) return FEW ? kFewWaves : 16;
     else return KT / R;
 }
 
@@ -612,19 +618,25 @@ constexpr int span_waves() {
 // keys of four rounds, but 32 steps at K = 8, P = 138M (eight rows, one wave a
 // block) 21.7 and 20.5 ms, and 100 at K = 16, P = 25.6M (four rows) 22.9 and 22.5
 // with one round's.  With one row a wave the launch is bound by HBM or by latency.
-template <int KT, int R>
+// Only 13 to 16 waves of four rows, one block a CU either way, have room for all (32
+// steps at K = 56, 160M elements, 3.38 and 3.41 ms).
+template <int KT, int R, bool FEW>
 constexpr int span_vector_keys() {
-    if constexpr (KT == 0) return R < 8 ? 8 : 0;
+    if constexpr (KT == 0) return R == 4 && !FEW ? 8 : 0;
     else if constexpr (KT == 1) return 8;
     else return KT == 32 && R == 8 ? 4 : 0;
 }
 
-// Waves per SIMD that k_span's registers leave room for, at least.
-template <int KT, int R>
+// Waves per SIMD that k_span's registers leave room for, at least.  With K an
+// argument they make room for two blocks a CU (some registers spill around a
+// measurement, none in the steps).  One and two blocks, x of 160M elements, a step
+// with its sync: K = 24 609 and 481 us, K = 28 617 and 561, K = 33 637 and 522; 32 steps
+// in one launch: K = 24 3.27 and 2.62 ms, K = 31 3.20 and 2.74, K = 33 3.52 and 3.02.
+template <int KT, int R, bool FEW>
 constexpr int span_occupancy() {
     if constexpr (R == 1) return KT == 0 ? 6 : (KT == 1 ? 7 : 8);
-    else if constexpr (R == 2) return KT == 0 ? 5 : (KT == 32 ? 8 : 7);
-    else if constexpr (R == 4) return KT == 0 ? 4 : 5;
+    else if constexpr (R == 2) return KT == 0 ? (FEW ? 6 : 8) : (KT == 32 ? 8 : 7);
+    else if constexpr (R == 4) return KT == 0 ? (FEW ? 6 : 4) : 5;
     else return 4;
 }
 
@@ -652,17 +664,30 @@ constexpr int span_occupancy() {
 // transcendental functions (8 cycles), about 250 cycles of issue in all.  With the steps launched one by one, then in
 // spans of two rows a wave, then so: 32 steps at K = 8, P = 138M 96.8 / 25.4 / 21.1
 // ms, 24 traced at K = 8, P = 11.2M 6.41 / 1.94 / 1.48 ms.
-template <int KT, int R, bool VEC, bool NT>
-__global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT, R>())) k_span(SpanParams p) {
-    constexpr int WMAX = span_waves<KT, R>();
+template <int KT, int R, bool VEC, bool NT, bool FEW = false>
+__global__ void __launch_bounds__((64 * span_waves<KT, R, FEW>()), (span_occupancy<KT, R, FEW>())) k_span(SpanParams p) {
+    constexpr int WMAX = span_waves<KT, R, FEW>();
     const StepParams &a = p.s;
     const int K = KT > 0 ? KT : a.K;
     const int W = KT > 0 ? WMAX : (K + R - 1) / R;
     // blocks of 8 and 16 waves form each group's mean once (group_means)
     constexpr bool SPLIT = KT > 0 && WMAX >= 8;
-    __shared__ f4 part[WMAX][64];
+    // part: the waves' sums of their rows; dev: of their squared deviations.  With K an
+    // argument they take what the launch gives them (span_lds), W waves' worth: with room
+    // for 16 a CU held six blocks of K = 3's three waves (a step with its sync, 160M
+    // elements, 536 us; so 502).
+    extern __shared__ f4 span_lds_base[];
+    __shared__ f4 part_s[KT > 0 ? WMAX : 1][64];
     __shared__ f4 means[SPLIT ? 64 : 1];
-    __shared__ double dev[WMAX][64];
+    __shared__ double dev_s[KT > 0 ? WMAX : 1][64];
+    auto part = [&](int i) -> f4 (&)[64] {
+        if constexpr (KT > 0) return part_s[i];
+        else return reinterpret_cast<f4 (*)[64]>(span_lds_base)[i];
+    };
+    auto dev = [&](int i) -> double (&)[64] {
+        if constexpr (KT > 0) return dev_s[i];
+        else return reinterpret_cast<double (*)[64]>(span_lds_base + 64 * W)[i];
+    };
     const SpanPlan sp = span_plan(p.when, p.sched, p.rule);
     if (sp.n == 0) return;
     const int lane = threadIdx.x & 63;
@@ -685,19 +710,35 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT
     const bool x_one = sp.merged_in, m_one = sp.merged_in && p.avg_m;
     f4 x[R], m[R], h, xs;
     if (whole) {
-        if (x_one) x[0] = ld4<false>(a.x + lo + e);
-        if (m_one) m[0] = ld4<false>(a.m + lo + e);
+        if constexpr (KT == 0) {
+            // every load goes out before one is waited for, as a copied row is
+            auto load_rows = [&](f4 *v, const float *rows, const float *row0, bool one) {
+                if (one) {
+                    const f4 v0 = ld4<false>(row0 + e);
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (!has[r]) {
-                x[r] = m[r] = splat(0.0f);
-                continue;
+                    for (int r = 0; r < R; ++r) v[r] = has[r] ? v0 : splat(0.0f);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) v[r] = has[r] ? ld4<NT>(rows + r * a.ld + e) : splat(0.0f);
+                }
+            };
+            h = ld4<false>(a.h + lo + e);
+            xs = ld4<false>(a.xs + lo + e);
+            load_rows(m, mb, a.m + lo, m_one);
+            load_rows(x, xb, a.x + lo, x_one);
+        } else {
+            // (with one row a wave a CU's 32 waves have more loads out so than HBM
+            // takes well: a step with its sync, K = 8, P = 20M, 459 us row by row, 494 so)
+            if (x_one) x[0] = ld4<false>(a.x + lo + e);
+            if (m_one) m[0] = ld4<false>(a.m + lo + e);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                x[r] = x_one ? x[0] : ld4<NT>(xb + r * a.ld + e);
+                m[r] = m_one ? m[0] : ld4<NT>(mb + r * a.ld + e);
             }
-            x[r] = x_one ? x[0] : ld4<NT>(xb + r * a.ld + e);
-            m[r] = m_one ? m[0] : ld4<NT>(mb + r * a.ld + e);
+            h = ld4<false>(a.h + lo + e);
+            xs = ld4<false>(a.xs + lo + e);
         }
-        h = ld4<false>(a.h + lo + e);
-        xs = ld4<false>(a.xs + lo + e);
     } else {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -715,7 +756,7 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT
     // the chunk's first tile and the next chunk's, in lanes 0 and 1: a vector
     // load, so that no wait for it comes ahead of the row loads
     const int32_t seg_l = p.chunk_seg[c + (lane & 1)];
-    const auto gd = group_data<span_vector_keys<KT, R>()>(a, g, h, xs);
+    const auto gd = group_data<span_vector_keys<KT, R, FEW>()>(a, g, h, xs);
     const int j0 = (int)(sp.t - p.when.t);   // the first step's rate is gamma[j0]
     int slot = 0;
 #pragma unroll 1
@@ -729,14 +770,14 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT
         // the mean of the K rows v at every lane (part and means are free on entry)
         auto row_mean = [&](const f4 *v) -> f4 {
             if constexpr (WMAX == 1) return tree_sum_regs<R>(v, 0) * splat(1.0f / (float)KT);
-            part[w][lane] = tree_sum_regs<R>(v, 0);   // (rows a ragged last wave lacks hold zeros)
+            part(w)[lane] = tree_sum_regs<R>(v, 0);   // (rows a ragged last wave lacks hold zeros)
             __syncthreads();
             if constexpr (SPLIT) {
-                group_means<WMAX, KT>(part, means, lane, w, 64);
+                group_means<WMAX, KT>(part_s, means, lane, w, 64);
                 __syncthreads();
                 return means[lane];
             }
-            return lds_mean<KT, WMAX, R>(part, lane, W, K);
+            return lds_mean<KT, WMAX, R>(&part(0), lane, W, K);
         };
         const f4 mean = row_mean(x);
         if (due && p.avg_m) {
@@ -768,14 +809,14 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R>()), (span_occupancy<KT
             if constexpr (KT > 0) v = tree_sum_regs_d<R>(q, 0);
             else v = q[0];
             if constexpr (WMAX > 1) {
-                dev[w][lane] = v;
+                dev(w)[lane] = v;
                 __syncthreads();
                 if (summer) {
                     if constexpr (KT > 0) {
-                        v = tree_sum_lds_d<WMAX>(dev, lane, 0);
+                        v = tree_sum_lds_d<WMAX>(dev_s, lane, 0);
                     } else {
-                        v = dev[0][lane];
-                        for (int i = 1; i < W; ++i) v += dev[i][lane];
+                        v = dev(0)[lane];
+                        for (int i = 1; i < W; ++i) v += dev(i)[lane];
                     }
                 }
                 if (CUT) __syncthreads();   // dev is read before the next tile's sums
@@ -1396,15 +1437,19 @@ hipError_t average_dispatch(const SyncParams &p, bool avg_m, bool vec, bool nt, 
     return average_variant<KT, false, false, false, RD, RAGGED>(p, cap, st);
 }
 
-template <int KT, int R>
+// Dynamic LDS of a k_span block of `waves` waves with K an argument: part and dev.
+constexpr int span_lds(int waves) { return waves * 64 * (int)(sizeof(f4) + sizeof(double)); }
+
+template <int KT, int R, bool FEW = false>
 hipError_t span_variant(const SpanParams &p, bool vec, bool nt, hipStream_t st) {
-    const int threads = KT > 0 ? 64 * span_waves<KT, R>() : 64 * any_k_waves(p.s.K);
+    const int threads = KT > 0 ? 64 * span_waves<KT, R, FEW>() : 64 * any_k_waves(p.s.K);
+    const int lds = KT > 0 ? 0 : span_lds(any_k_waves(p.s.K));
     return in_pieces(p.n_chunks, threads, [&](int64_t b0, unsigned nb) {   // a block per chunk
         SpanParams q = p;
         q.s.block0 = b0;
-        if (vec && nt) k_span<KT, R, true, true><<<dim3(nb), dim3(threads), 0, st>>>(q);
-        else if (vec) k_span<KT, R, true, false><<<dim3(nb), dim3(threads), 0, st>>>(q);
-        else k_span<KT, R, false, false><<<dim3(nb), dim3(threads), 0, st>>>(q);
+        if (vec && nt) k_span<KT, R, true, true, FEW><<<dim3(nb), dim3(threads), lds, st>>>(q);
+        else if (vec) k_span<KT, R, true, false, FEW><<<dim3(nb), dim3(threads), lds, st>>>(q);
+        else k_span<KT, R, false, false, FEW><<<dim3(nb), dim3(threads), lds, st>>>(q);
     });
 }
 
@@ -1423,8 +1468,8 @@ template <int KT, int WIDE, int MID, int TALL>
 hipError_t span_dispatch(const SpanParams &p, bool vec, bool nt, hipStream_t st) {
     auto fills = [&](int waves) { return p.n_chunks * waves >= 2 * kSimds; };
     if (p.when.n >= 3 || KT == 32) {
-        if (fills(span_waves<KT, TALL>())) return span_variant<KT, TALL>(p, vec, nt, st);
-        if (fills(span_waves<KT, MID>())) return span_variant<KT, MID>(p, vec, nt, st);
+        if (fills(span_waves<KT, TALL, false>())) return span_variant<KT, TALL>(p, vec, nt, st);
+        if (fills(span_waves<KT, MID, false>())) return span_variant<KT, MID>(p, vec, nt, st);
     }
     return span_variant<KT, WIDE>(p, vec, nt, st);
 }
@@ -1536,10 +1581,11 @@ hipError_t launch_span(const SpanParams &p, int64_t n_tiles, bool vec, bool nt, 
     default: break;
     }
     if (any_k_kernel(K, false)) {
+        const bool few = any_k_waves(K) <= kFewWaves;
         switch (any_k_rows(K)) {
-        case 1: return span_variant<0, 1>(p, vec, nt, st);
-        case 2: return span_variant<0, 2>(p, vec, nt, st);
-        case 4: return span_variant<0, 4>(p, vec, nt, st);
+        case 1: return span_variant<0, 1, true>(p, vec, nt, st);
+        case 2: return few ? span_variant<0, 2, true>(p, vec, nt, st) : span_variant<0, 2>(p, vec, nt, st);
+        case 4: return few ? span_variant<0, 4, true>(p, vec, nt, st) : span_variant<0, 4>(p, vec, nt, st);
         default: return span_variant<0, 8>(p, vec, nt, st);
         }
     }

@@ -64,7 +64,8 @@ def _by_hand(A, w, n, pad=True):
 # rows per wave two waves per SIMD, just, 3,000 elements none
 @pytest.mark.parametrize("avg_m", [False, True])
 @pytest.mark.parametrize("K,P", [(1, 3000), (2, 530_001), (4, 270_001), (8, 140_001), (16, 140_001), (32, 70_001), (8, 3000),
-                                 (32, 3000), (4, 524_289), (8, 524_035), (32, 131_073), (3, 9001), (7, 9001), (24, 9001), (33, 5001), (64, 5001), (65, 3001),
+                                 (32, 3000), (4, 524_289), (8, 524_035), (32, 131_073), (3, 9001), (7, 9001), (24, 9001), (25, 9001), (31, 5001), (33, 5001), (48, 5001), (49, 5001),
+                                 (64, 5001), (65, 3001),
                                  (100, 3001), (128, 3000), (129, 2001)])
 def test_run_equals_one_step_launches(A, K, P, avg_m):
     """A constant-period run (whole spans of syncs) against single-step launches:
