@@ -1074,6 +1074,11 @@ __global__ void __launch_bounds__(kBlock) k_reduce_chunks(ReduceParams r) {
 
 constexpr int kFinishThreads = 256;
 constexpr int kFinishTensors = 512;   // tensors whose sums the finishing block keeps in LDS
+// Slots that one finishing block takes in turn, decisions and all: a launch less than a
+// block for each and k_control.  A traced adaptive run at p = 1 reserves up to four a
+// launch and mostly fills one: 140 steps, K = 4, P = 65,536 2.37 ms with k_control, 1.97
+// so; at p = 4, where most are filled, 0.88 and 0.89.
+constexpr unsigned kSerialSlots = 4;
 
 // Level 2 for problems with more chunk partials than one LDS window: one block
 // per window of tensors (blockIdx.x) and slot (blockIdx.y).  A window of small
@@ -1146,128 +1151,139 @@ __global__ void __launch_bounds__(kFinishThreads) k_reduce_windows(ReduceParams 
     }
 }
 
-// Level 2 and the decision, one block per slot.  With at most kFinishWindow
-// chunk partials (n_windows = 0) it sums the tensors itself, in a fixed order
-// chosen by the tensor's chunk count: a tensor of at most kSmallTensorChunks
+// Level 2 and the decision, one block per slot, or one for all slots in turn.  With at
+// most kFinishWindow chunk partials (n_windows = 0) it sums the tensors itself, in a
+// fixed order chosen by the tensor's chunk count: a tensor of at most kSmallTensorChunks
 // chunks is owned by one thread, which adds its chunks from LDS (four
 // interleaved partial sums); a larger tensor is owned by one wave, whose lanes
 // add strided chunks from LDS before a butterfly; then out[tau] = variance
 // (deviation sum / K), out[T + tau] = gradient norm^2, and S and the norm total
 // are block sums.  Otherwise k_reduce_windows has written out, and S and the
 // norm total are block sums of its window partials.  With a controller on the
-// device and one slot, thread 0 then takes Algorithm 2's decision; with several
-// slots it leaves the sums to k_control, which takes them in step order; with
-// none it writes the record itself, nothing of which moves at a sync.  out and
-// the record header are the host's pinned record slot, written directly.
+// device a single block's thread 0 then takes Algorithm 2's decisions in step order;
+// several blocks leave the sums to k_control, which does.  With none it writes the
+// record itself, nothing of which moves at a sync.  out and the record header are
+// the host's pinned record slot, written directly.
+template <bool ALL>   // one block for all slots
 __global__ void __launch_bounds__(kFinishThreads) k_reduce_finish(ReduceParams r) {
     __shared__ double la[kFinishWindow], lb[kFinishWindow];
     __shared__ double lacc[2 * kFinishTensors];   // per-tensor sums, where they fit
-    const int slot = blockIdx.x;
     fetch_args<offsetof(ReduceParams, gamma)>();
-    if (r.n_windows == 0) {
+    const bool decide = r.control && (ALL || r.n_slots == 1);
+    auto load_partials = [&](int slot) {
+        if (r.n_windows > 0) return;
         // every chunk partial fits one LDS window (the host cuts the tensors into
-        // windows for k_reduce_windows otherwise); the loads are under way while
-        // the plan is worked out (of a slot without a measurement they are not used)
+        // windows for k_reduce_windows otherwise)
         const double *cp = r.chunk_partials + slot * r.chunk_stride;
         for (int32_t i = (int32_t)threadIdx.x; i < r.n_chunks; i += kFinishThreads) {
             la[i] = cp[2 * (int64_t)i];
             lb[i] = cp[2 * (int64_t)i + 1];
         }
-    }
+    };
+    // (the loads are under way while the plan is worked out; of a slot without a
+    // measurement they are not used)
+    load_partials(blockIdx.x);
     const SpanPlan sp = span_plan(r.when, r.sched, r.rule);
-    int j;
+    SchedState st{};   // (thread 0's)
+    int slot = blockIdx.x, j;
     bool due;
-    if (!slot_step(r, sp, slot, &j, &due)) {
-        __syncthreads();   // every thread has read the controller state
-        if (threadIdx.x == 0 && r.n_slots == 1 && r.control) {
-            SchedState st = *r.sched;
-            write_hdr(slot_hdr(r, 0), sp.t + sp.n - 1, sp.n, false, st.p, st.p, ADPSGD_OK, 0.0, 0.0, st.C2, st.nC2);
-            end_span(r, sp, &st);
-            *r.sched = st;
+    for (; slot < r.n_slots && slot_step(r, sp, slot, &j, &due); ++slot) {
+        if (ALL && slot > 0) {
+            __syncthreads();   // la, lb and lacc of the slot before are read
+            load_partials(slot);
         }
-        return;
-    }
-    double *out = reinterpret_cast<double *>(reinterpret_cast<char *>(slot_hdr(r, slot)) + kSlotHdrBytes);
-    double sa = 0.0, sb = 0.0;
-    if (r.n_windows > 0) {
-        // the tensors were reduced by k_reduce_windows: add the window sums
-        const double *wp = r.win_partials + (int64_t)slot * 2 * r.n_windows;
-        for (int32_t w = (int32_t)threadIdx.x; w < r.n_windows; w += kFinishThreads) {
-            sa += wp[2 * w];
-            sb += wp[2 * w + 1];
-        }
-    } else {
-        double *acc = r.T <= kFinishTensors ? lacc : r.acc + (int64_t)slot * 2 * r.T;
-        __syncthreads();   // la, lb
-        // small tensors: a thread each
-        for (int32_t tau = (int32_t)threadIdx.x; tau < r.T; tau += kFinishThreads) {
-            const int32_t b = r.chunk_begin[tau], e = r.chunk_begin[tau + 1];
-            if (e - b > kSmallTensorChunks || b >= e) continue;
-            double a[4] = {0.0, 0.0, 0.0, 0.0}, g[4] = {0.0, 0.0, 0.0, 0.0};
-            int32_t i = b;
-            for (; i + 4 <= e; i += 4) {
+        double *out = reinterpret_cast<double *>(reinterpret_cast<char *>(slot_hdr(r, slot)) + kSlotHdrBytes);
+        double sa = 0.0, sb = 0.0;
+        if (r.n_windows > 0) {
+            // the tensors were reduced by k_reduce_windows: add the window sums
+            const double *wp = r.win_partials + (int64_t)slot * 2 * r.n_windows;
+            for (int32_t w = (int32_t)threadIdx.x; w < r.n_windows; w += kFinishThreads) {
+                sa += wp[2 * w];
+                sb += wp[2 * w + 1];
+            }
+        } else {
+            double *acc = r.T <= kFinishTensors ? lacc : r.acc + (int64_t)slot * 2 * r.T;
+            __syncthreads();   // la, lb
+            // small tensors: a thread each
+            for (int32_t tau = (int32_t)threadIdx.x; tau < r.T; tau += kFinishThreads) {
+                const int32_t b = r.chunk_begin[tau], e = r.chunk_begin[tau + 1];
+                if (e - b > kSmallTensorChunks || b >= e) continue;
+                double a[4] = {0.0, 0.0, 0.0, 0.0}, g[4] = {0.0, 0.0, 0.0, 0.0};
+                int32_t i = b;
+                for (; i + 4 <= e; i += 4) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    a[q] += la[i + q];
-                    g[q] += lb[i + q];
+                    for (int q = 0; q < 4; ++q) {
+                        a[q] += la[i + q];
+                        g[q] += lb[i + q];
+                    }
+                }
+                if (i < e) { a[0] += la[i]; g[0] += lb[i]; }
+                if (i + 1 < e) { a[1] += la[i + 1]; g[1] += lb[i + 1]; }
+                if (i + 2 < e) { a[2] += la[i + 2]; g[2] += lb[i + 2]; }
+                acc[tau] = (a[0] + a[1]) + (a[2] + a[3]);
+                acc[r.T + tau] = (g[0] + g[1]) + (g[2] + g[3]);
+            }
+            // large tensors (listed by the host): a wave each, strided lanes, then
+            // a butterfly
+            const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+            for (int32_t k = wave; k < r.n_large; k += kFinishThreads / 64) {
+                const int32_t tau = r.large[k];
+                const int32_t cb = r.chunk_begin[tau], ce = r.chunk_begin[tau + 1];
+                double a = 0.0, g = 0.0;
+                for (int32_t i = cb + lane; i < ce; i += 64) {
+                    a += la[i];
+                    g += lb[i];
+                }
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) {
+                    a += __shfl_xor(a, off, 64);
+                    g += __shfl_xor(g, off, 64);
+                }
+                if (lane == 0) {
+                    acc[tau] = a;
+                    acc[r.T + tau] = g;
                 }
             }
-            if (i < e) { a[0] += la[i]; g[0] += lb[i]; }
-            if (i + 1 < e) { a[1] += la[i + 1]; g[1] += lb[i + 1]; }
-            if (i + 2 < e) { a[2] += la[i + 2]; g[2] += lb[i + 2]; }
-            acc[tau] = (a[0] + a[1]) + (a[2] + a[3]);
-            acc[r.T + tau] = (g[0] + g[1]) + (g[2] + g[3]);
-        }
-        // large tensors (listed by the host): a wave each, strided lanes, then
-        // a butterfly
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        for (int32_t k = wave; k < r.n_large; k += kFinishThreads / 64) {
-            const int32_t tau = r.large[k];
-            const int32_t cb = r.chunk_begin[tau], ce = r.chunk_begin[tau + 1];
-            double a = 0.0, g = 0.0;
-            for (int32_t i = cb + lane; i < ce; i += 64) {
-                a += la[i];
-                g += lb[i];
-            }
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                a += __shfl_xor(a, off, 64);
-                g += __shfl_xor(g, off, 64);
-            }
-            if (lane == 0) {
-                acc[tau] = a;
-                acc[r.T + tau] = g;
+            __syncthreads();  // acc of the large tensors, for their owner threads below
+            for (int32_t tau = (int32_t)threadIdx.x; tau < r.T; tau += kFinishThreads) {
+                double v = 0.0, g = 0.0;
+                if (r.chunk_begin[tau + 1] > r.chunk_begin[tau]) {
+                    v = acc[tau] / (double)r.K;
+                    g = acc[r.T + tau];
+                }
+                out[tau] = v;
+                out[r.T + tau] = g;
+                sa += v;
+                sb += g;
             }
         }
-        __syncthreads();  // acc of the large tensors, for their owner threads below
-        for (int32_t tau = (int32_t)threadIdx.x; tau < r.T; tau += kFinishThreads) {
-            double v = 0.0, g = 0.0;
-            if (r.chunk_begin[tau + 1] > r.chunk_begin[tau]) {
-                v = acc[tau] / (double)r.K;
-                g = acc[r.T + tau];
+        const Pair tot = block_sum2<kFinishThreads / 64>(sa, sb);
+        if (threadIdx.x == 0) {
+            if (decide) {
+                if (slot == 0) st = *r.sched;
+                control_slot(r, sp, slot, j, due, tot.a, tot.b, &st);
+            } else if (r.control) {
+                r.sums[2 * slot] = tot.a;
+                r.sums[2 * slot + 1] = tot.b;
+            } else {
+                // (no p, C2 or nC2: they are the host's alone here, and a captured launch
+                // serves runs from states that differ in them)
+                write_hdr(slot_hdr(r, slot), sp.t + j, sp.n, due, 0, 0,
+                          __builtin_isfinite(tot.a) ? ADPSGD_OK : ADPSGD_ENONFINITE, tot.a, tot.b, 0.0, 0);
             }
-            out[tau] = v;
-            out[r.T + tau] = g;
-            sa += v;
-            sb += g;
         }
+        if (!ALL) break;
     }
-    const Pair tot = block_sum2<kFinishThreads / 64>(sa, sb);
+    if (!decide) return;
+    const bool none = !slot_step(r, sp, 0, &j, &due);   // no measurement
+    if (none) __syncthreads();                         // every thread has read the controller state
     if (threadIdx.x == 0) {
-        if (r.control && r.n_slots == 1) {
-            SchedState st = *r.sched;
-            control_slot(r, sp, 0, j, due, tot.a, tot.b, &st);
-            end_span(r, sp, &st);
-            *r.sched = st;
-        } else if (r.control) {
-            r.sums[2 * slot] = tot.a;
-            r.sums[2 * slot + 1] = tot.b;
-        } else {
-            // (no p, C2 or nC2: they are the host's alone here, and a captured launch
-            // serves runs from states that differ in them)
-            write_hdr(slot_hdr(r, slot), sp.t + j, sp.n, due, 0, 0,
-                      __builtin_isfinite(tot.a) ? ADPSGD_OK : ADPSGD_ENONFINITE, tot.a, tot.b, 0.0, 0);
+        if (none) {
+            st = *r.sched;
+            write_hdr(slot_hdr(r, 0), sp.t + sp.n - 1, sp.n, false, st.p, st.p, ADPSGD_OK, 0.0, 0.0, st.C2, st.nC2);
         }
+        end_span(r, sp, &st);
+        *r.sched = st;
     }
 }
 
@@ -1651,9 +1667,11 @@ hipError_t launch_reduce(const ReduceParams &r, hipStream_t st) {
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    k_reduce_finish<<<dim3(slots), dim3(kFinishThreads), 0, st>>>(r);
+    const bool all = r.control && slots > 1 && slots <= kSerialSlots;
+    if (all) k_reduce_finish<true><<<dim3(1), dim3(kFinishThreads), 0, st>>>(r);
+    else k_reduce_finish<false><<<dim3(slots), dim3(kFinishThreads), 0, st>>>(r);
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !r.control || slots == 1) return e;
+    if (e != hipSuccess || !r.control || all || slots == 1) return e;
     k_control<<<dim3(1), dim3(64), 0, st>>>(r);
     return hipGetLastError();
 }

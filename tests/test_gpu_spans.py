@@ -115,6 +115,24 @@ def test_adaptive_periods_agree_under_every_policy(A, K, p, N, traced):
     assert len(r[0]) > 1 and out[0] == out[1] == out[2]
 
 
+# launches of up to 4 and of more measurements whose decisions the device takes (one
+# finishing block, or one for each and a kernel for the decisions), on every path of
+# the reduction: tensors summed in LDS, in device memory (over 512), in windows
+@pytest.mark.parametrize("p", [1, 2, 3, 4, 6])
+@pytest.mark.parametrize("sizes", [(2000, 7, 1500), (40,) * 600, (3,) * 3600 + (70_000, 5)])
+def test_decisions_of_several_measurements_agree_under_every_policy(A, sizes, p):
+    w = _w(K=4, sizes=sizes, p_init=p, total_steps=60, period_mode=W.PERIOD_ADAPTIVE, k_s=2 * p, lr_kind=W.LR_STEP)
+    out = []
+    for pol in (A.LAUNCH_HYBRID, A.LAUNCH_DEVICE, A.LAUNCH_HOST):
+        with A.Adpsgd.from_workload(w) as eng:
+            eng.set_launch_policy(pol)
+            recs, var, _, steps = eng.run_traced(60)
+            st = eng.get_state()
+            out.append((recs.tobytes(), var.tobytes(), steps.tobytes(), eng.x.cpu().numpy().tobytes(),
+                        (st.t, st.cnt, st.p, st.nC2, st.C2)))
+    assert out[0] == out[1] == out[2]
+
+
 @pytest.mark.parametrize("avg_m", [False, True])
 @pytest.mark.parametrize("K,mode,pol", [(4, W.PERIOD_CONST, "HYBRID"), (8, W.PERIOD_ADAPTIVE, "HYBRID"),
                                         (5, W.PERIOD_ADAPTIVE, "HOST"), (16, W.PERIOD_ALG1, "HYBRID")])
