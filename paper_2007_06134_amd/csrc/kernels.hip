@@ -127,7 +127,10 @@ __device__ __forceinline__ GroupData<ROUNDS> group_data(const StepParams &a, int
     }
     // Four consecutive registers each, as loaded: scattered over the register file the
     // same instructions run 5% slower (32 steps at K = 8, P = 138M 22.0 ms, not 20.9).
-    asm("" : "+v"(hw), "+v"(c), "+v"(b));
+    // With eight rows a wave at K = 32 (ROUNDS = 4), where registers are short, only c: 400
+    // steps at P = 1.2M 9.51 ms, and 9.91 with all three.
+    if constexpr (ROUNDS == 4) asm("" : "+v"(c));
+    else asm("" : "+v"(hw), "+v"(c), "+v"(b));
     return GroupData<ROUNDS>{hw, c, b, philox_group((uint32_t)g, a.rk),
                              noise_keys<ROUNDS>(a.rk), in_vgpr(a.sigma_r), in_vgpr(a.mu)};
 }
