@@ -12,8 +12,9 @@ several steps and their syncs in one pass over x and m, so the roofline entry
 is the issue rate of a step's instructions: K P updates over a step's share of
 its launch (HIP events recorded on the library's stream during the timed
 region, around every 8th launch of each kernel kind, --timing-every, so that
-the events barely disturb the job), against the rate at which eight waves a
-SIMD issue the step alone.
+the events barely disturb the job), against the rate at which the device's
+SIMDs can issue them (ISSUE_PEAK).  The bytes of the passes over the run's time
+stand beside it (hbm).
 
 Prints one JSON line.
 """
@@ -30,9 +31,16 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-# 256 updates (a wave's step of one worker) on each of 1024 SIMDs every 112 ns
-ISSUE_PEAK = 256 * 1024 / 112e-9
+# Vector instructions of a wave's step of one worker (256 updates; counted in the
+# compiled step loop of k_local_step): products of two 32-bit words, transcendental
+# functions, and fp32 and 32-bit integer operations.  A SIMD issues one of them in at
+# least 4, 8 and 2 cycles (64 lanes over 16, 8 and 32 a cycle); the device has 256 CUs of four
+# SIMDs at up to 2.4 GHz.
+STEP_INSTRUCTIONS = {"products": (16, 4), "transcendental": (8, 8), "others": (49, 2)}
+ISSUE_PEAK = 256 * 1024 * 2.4e9 / sum(n * cycles for n, cycles in STEP_INSTRUCTIONS.values())
+HBM_PEAK = 8.0e12
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "local_step_k8_p138m_traffic.md")
+SPAN_FILE = os.path.join(ROOT, "profiles", "span_k8_p138m_counters.md")
 
 
 def code_tokens(text: str) -> str:
@@ -89,6 +97,33 @@ def measured_traffic(w, block, lds, row_chunks):
     if not (m_d and m_b) or m_d.group(1) != kernel_source_digest():
         return None
     return float(m_b.group(1))
+
+
+def measured_span_traffic(w):
+    """HBM bytes per pass of k_span (averaged over a whole run) from the committed
+    counter summary, if it was taken on the current kernel sources and w is its
+    workload; else None."""
+    if w.name != "k8_p138m_t32_adaptive" or not os.path.exists(SPAN_FILE):
+        return None
+    txt = open(SPAN_FILE).read()
+    m_d = re.search(r"kernel sources digest:\s*`?([0-9a-f]{16})", txt)
+    m_b = re.search(r"HBM bytes per pass \(scaled\):\s*([0-9.eE+]+)", txt)
+    if not (m_d and m_b) or m_d.group(1) != kernel_source_digest():
+        return None
+    return float(m_b.group(1))
+
+
+def least_hbm_bytes(w, sync_t):
+    """(passes, bytes) that an adaptive run with syncs after the steps sync_t cannot do
+    without, passes over x and m: one up to the first sync whose outcome may move
+    the period, and one behind each such sync but a final one, which reads and
+    writes all rows of m, and of the merged replicas row 0, and reads h and x*.
+    None for schedules that are known in advance."""
+    import workloads as W
+    if w.period_mode != W.PERIOD_ADAPTIVE:
+        return None
+    passes = 1 + sum(1 for t in sync_t if t >= w.k_s and t + 1 < w.total_steps)
+    return passes, passes * (8 * w.K * w.P + 16 * w.P)
 
 
 def period_text(w) -> str:
@@ -225,7 +260,6 @@ def main():
     eng.close()
 
     updates = w.K * w.P * N * args.steps
-    step_bytes = 16 * w.K * w.P + 8 * w.P          # x, m read+write per worker; h, x* once
     out = {
         "metric": "param-updates/s",
         "value": updates / elapsed,
@@ -253,26 +287,31 @@ def main():
     if tm.step_launches > 0:
         step_ms = tm.step_ms / tm.step_launches
         achieved = w.K * w.P / (step_ms * 1e-3)
-        traffic = measured_traffic(w, step_block, step_lds, step_row_chunks)
+        traffic = measured_span_traffic(w)
         out["roofline"] = {"bound": "vector issue", "achieved": achieved, "peak": ISSUE_PEAK,
                            "unit": "param-updates/s", "frac": achieved / ISSUE_PEAK, "traffic": traffic,
-                           # traffic (of a launch of one local step) is not measured in this
-                           # run: it is the copy-scaled FETCH_SIZE + WRITE_SIZE of a separate
-                           # rocprofv3 --pmc run, read from the committed summary when it was
-                           # taken on these kernel sources and this launch shape (else null)
-                           "traffic_source": {"profile": os.path.relpath(TRAFFIC_FILE, ROOT),
+                           # traffic (bytes of a pass) is not measured in this run: it is the
+                           # copy-scaled FETCH_SIZE + WRITE_SIZE of a separate rocprofv3 --pmc
+                           # run, read from the committed summary when it was taken on these
+                           # kernel sources (else null)
+                           "traffic_source": {"profile": os.path.relpath(SPAN_FILE, ROOT),
                                               "kernel_sources_digest": kernel_source_digest(),
                                               "matched": traffic is not None},
+                           # bytes of a launch of one local step in this launch shape, likewise
+                           "local_step_traffic": measured_traffic(w, step_block, step_lds, step_row_chunks),
                            "kernel": "k_span",
                            "local_step_block": step_block, "lds_reserved_per_block": step_lds,
                            "row_chunks": step_row_chunks, "row_stride": row_stride,
-                           "bytes_per_pass": step_bytes,
-                           "avg_launch_ms": step_ms, "timed_launches": tm.step_launches,
+                           # a step's share of its launch, whether a sync follows it or not
+                           "avg_step_ms": step_ms, "timed_steps": tm.step_launches + tm.fused_launches,
                            "timed_every": args.timing_every}
-        if tm.fused_launches > 0:
-            fused_ms = tm.fused_ms / tm.fused_launches
-            out["fused_step_sync"] = {"avg_launch_ms": fused_ms,
-                                      "segsum_avg_ms": tm.segsum_ms / max(tm.segsum_launches, 1)}
+    if tm.segsum_launches > 0:
+        out["reduction"] = {"avg_ms_per_measurement": tm.segsum_ms / tm.segsum_launches}
+    least = None if args.traced else least_hbm_bytes(w, recs["t"])
+    if least:
+        rate = least[1] * args.steps / elapsed
+        out["hbm"] = {"passes_at_least": least[0], "bytes_at_least": least[1], "achieved_GBs": rate / 1e9,
+                      "frac": rate / HBM_PEAK}
     if sep:
         out["separate_sync"] = sep
     if not args.no_timing:

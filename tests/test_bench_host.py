@@ -41,6 +41,27 @@ def test_traffic_is_read_for_the_launch_shape_and_current_sources(bench, tmp_pat
     assert bench.measured_traffic(W.parity_workloads()["resnet18_like"], 64, 0, 1) is None
 
 
+def test_span_traffic_is_read_for_its_workload_and_current_sources(bench, tmp_path, monkeypatch):
+    w = W.full_workloads()["vgg16_adaptive"]
+    f = tmp_path / "span.md"
+    monkeypatch.setattr(bench, "SPAN_FILE", str(f))
+    assert bench.measured_span_traffic(w) is None             # no summary
+    f.write_text(f"kernel sources digest: `{bench.kernel_source_digest()}`\n\nHBM bytes per pass (scaled): 1.25e+10\n")
+    assert bench.measured_span_traffic(w) == 1.25e10
+    assert bench.measured_span_traffic(W.full_workloads()["vgg16_const8"]) is None
+    f.write_text(f"kernel sources digest: `{'0' * 16}`\n\nHBM bytes per pass (scaled): 1.25e+10\n")
+    assert bench.measured_span_traffic(w) is None
+
+
+def test_least_passes_of_a_run(bench):
+    """One pass up to the first sync that may move p, one behind each such sync but a final one."""
+    w = W.full_workloads()["vgg16_adaptive"].replace(total_steps=20, k_s=8)
+    assert bench.least_hbm_bytes(w, [3, 7, 11, 15, 19]) == (3, 3 * (8 * w.K + 16) * w.P)
+    assert bench.least_hbm_bytes(w, [3, 7, 11, 16])[0] == 3
+    assert bench.least_hbm_bytes(w, [3, 7])[0] == 1
+    assert bench.least_hbm_bytes(w.replace(period_mode=W.PERIOD_CONST), [3, 7, 11]) is None
+
+
 def test_more_than_one_gpu_is_refused(bench, monkeypatch, capsys):
     monkeypatch.setattr("sys.argv", ["bench.py", "--gpus", "2"])
     with pytest.raises(SystemExit) as e:
