@@ -80,12 +80,14 @@ extern "C" {
                                    can plan (up to 64 steps and 16 syncs), up to and with
                                    the first sync whose outcome may move the period; behind
                                    such a sync the device ends launches itself, each with
-                                   its next sync, up to 3 ahead of the host.  A run in a
+                                   its next sync, up to 3 ahead of the host (with K above
+                                   128 one step at a time while p is 1 or 2; else the host
+                                   reads the decision first).  A run in a
                                    constant-period mode on a problem of K * P < 2^24
                                    (launch-bound) and up to 65536 steps, with timing off,
                                    is captured once as a HIP graph of the same launches and
-                                   replayed while runs repeat with the same start state,
-                                   length and step launch shape                            */
+                                   replayed while runs repeat with the same t, cnt and p at
+                                   the start, length and step launch shape                 */
 #define ADPSGD_LAUNCH_DEVICE 1  /* every step is a launch, decided on the device (step +
                                    optional sync + reduction per step)                     */
 #define ADPSGD_LAUNCH_HOST 2    /* the host waits for every decision it needs; the device

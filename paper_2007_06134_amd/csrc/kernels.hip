@@ -663,10 +663,12 @@ constexpr int span_occupancy() {
 // controller state, says is due (when.device; span_plan).
 //
 // Bound: a span of one step by HBM, of five and more by vector arithmetic: a row's
-// step is 73 instructions, among them 16 32-bit products (4 cycles a wave) and 8
-// transcendental functions (8 cycles), about 250 cycles of issue in all.  With the steps launched one by one, then in
-// spans of two rows a wave, then so: 32 steps at K = 8, P = 138M 96.8 / 25.4 / 21.1
-// ms, 24 traced at K = 8, P = 11.2M 6.41 / 1.94 / 1.48 ms.
+// step is 68 to 73 instructions, among them 16 32-bit products (at least 4 cycles a
+// wave) and 8 transcendental functions (8 cycles), at least 216 cycles of issue in all;
+// at K = 8, P = 138M a SIMD issues one every 3.6 cycles, where these limits give 3.2.
+// With the steps launched one by one, then in spans of two rows a wave, then so: 32
+// steps at K = 8, P = 138M 96.8 / 25.4 / 21.1 ms, 24 traced at K = 8, P = 11.2M 6.41 /
+// 1.94 / 1.50 ms.
 template <int KT, int R, bool VEC, bool NT, bool FEW = false>
 __global__ void __launch_bounds__((64 * span_waves<KT, R, FEW>()), (span_occupancy<KT, R, FEW>())) k_span(SpanParams p) {
     constexpr int WMAX = span_waves<KT, R, FEW>();
@@ -1473,9 +1475,11 @@ hipError_t span_variant(const SpanParams &p, bool vec, bool nt, hipStream_t st) 
 }
 
 // A compiled K runs a span in one of three layouts.  One row per wave (two at K =
-// 32) streams best and has the most waves: one and two steps, bound by HBM (K = 8,
-// P = 11.2M, single steps with their sync 1.08 ms for four against 1.13 with eight
-// rows per wave).  More rows per wave share the lanes' Philox products and the
+// 32) streams best and has the most waves: launches of one and two steps, bound by HBM
+// (K = 8, P = 11.2M, single steps with their sync 1.08 ms for four against 1.13 with
+// eight rows per wave).  What counts is the most steps that the launch may take: one
+// that the device ends, with an adaptive period of 1 or 2, may take 3 to 5 and has more
+// rows per wave, although it mostly ends sooner.  More rows per wave share the lanes' Philox products and the
 // work of a sync, and with all rows in one wave a sync needs no barrier: 32 steps at
 // K = 8, P = 138M 22.3 ms with two rows per wave, 20.6 with eight; 60 steps at K =
 // 4, P = 20M 3.70 (two) and 3.44 (four); 400 at K = 32, P = 1.2M 10.1-11.1 (four)

@@ -4,8 +4,9 @@
 // as 1, 2, 3", SC'11): ten rounds of two 32x32->64 multiplies by fixed odd
 // multipliers, with the high halves xored into the other two counter words
 // and the round key; the key advances by two Weyl constants per round.  The
-// key is the 64-bit seed split into two words; it is uniform across a launch,
-// so the ten round keys live in scalar registers.
+// key is the 64-bit seed split into two words; it is uniform across a launch.
+// The round keys are in scalar registers, or in vector registers where a kernel has
+// some to spare (noise_keys).
 //
 // Gaussian noise by Box-Muller (1958) on the 24 high bits of each word.
 #pragma once

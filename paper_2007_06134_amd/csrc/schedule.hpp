@@ -89,13 +89,14 @@ ADPSGD_HD bool apply_sync(const SchedRule &r, int64_t t, double gamma, double S,
     return true;
 }
 
+constexpr int kSpanSteps = 64;   // steps per launch at most
+
 // Which steps a launch takes and which of them a sync follows.  The host plans
 // both (device = 0: steps t .. t + n - 1, bit j of syncs set when a sync follows
 // step t + j), or the launch ends with the first step that the device's
 // controller state says is due, after n steps or before step `end`, whichever
 // comes first; it starts at t (known) or at the state's next step, which is then
 // at most kSpanSteps - 1 beyond t, the step of the launch's first rate.
-constexpr int kSpanSteps = 64;   // steps per launch at most
 //
 // Merged rows: behind a sync the K rows of x are equal (and of m, where momentum
 // is averaged), so inside a run a launch that ends with a sync writes row 0
