@@ -565,6 +565,23 @@ __device__ __forceinline__ double wave_sum(double v) {
     return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
 }
 
+// A whole group of a row that is 16-byte aligned (VEC) or only as its elements are:
+// global memory takes dwordx4 accesses at any multiple of four bytes, in place of
+// four that each touch all of a wave's kilobyte.  A step with its sync, packed rows of
+// 100M elements in all, with four single accesses and so: K = 8 587 and 358 us, K = 48
+// 688 and 415 (with one step a launch 643 and 559).
+typedef float f4_unaligned __attribute__((ext_vector_type(4), aligned(4)));
+template <bool VEC, bool NT>
+__device__ __forceinline__ f4 ld_group(const float *p) {
+    if constexpr (VEC) return ld4<NT>(p);
+    else return *reinterpret_cast<const f4_unaligned *>(p);
+}
+template <bool VEC, bool NT>
+__device__ __forceinline__ void st_group(float *p, f4 v) {
+    if constexpr (VEC) st4<NT>(p, v);
+    else *reinterpret_cast<f4_unaligned *>(p) = v;
+}
+
 // Access to the first `left` elements of a group (at most 4; none when left <= 0).
 __device__ __forceinline__ f4 ld4_left(const float *base, int left) {
     f4 v = splat(0.0f);
@@ -702,8 +719,8 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R, FEW>()), (span_occupan
     const int64_t g = (lo >> 2) + lane;
     const int e = 4 * lane;                // the lane's first element in the chunk
     const int len = (int)(hi - lo), left = len - e;
-    // the whole chunk moves as float4 groups (uniform), or single lanes are cut or unaligned
-    const bool whole = VEC && len == (int)kTileElems;
+    // the whole chunk moves as float4 groups (uniform), or single lanes are cut
+    const bool whole = len == (int)kTileElems;
     const bool full = VEC && left >= 4;
     bool has[R];   // row R w + r exists (uniform; only the last wave's last rows can be missing)
 #pragma unroll
@@ -719,12 +736,12 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R, FEW>()), (span_occupan
             // every load goes out before one is waited for, as a copied row is
             auto load_rows = [&](f4 *v, const float *rows, const float *row0, bool one) {
                 if (one) {
-                    const f4 v0 = ld4<false>(row0 + e);
+                    const f4 v0 = ld_group<VEC, false>(row0 + e);
 #pragma unroll
                     for (int r = 0; r < R; ++r) v[r] = has[r] ? v0 : splat(0.0f);
                 } else {
 #pragma unroll
-                    for (int r = 0; r < R; ++r) v[r] = has[r] ? ld4<NT>(rows + r * a.ld + e) : splat(0.0f);
+                    for (int r = 0; r < R; ++r) v[r] = has[r] ? ld_group<VEC, NT>(rows + r * a.ld + e) : splat(0.0f);
                 }
             };
             h = ld4<false>(a.h + lo + e);
@@ -734,12 +751,12 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R, FEW>()), (span_occupan
         } else {
             // (with one row a wave a CU's 32 waves have more loads out so than HBM
             // takes well: a step with its sync, K = 8, P = 20M, 459 us row by row, 494 so)
-            if (x_one) x[0] = ld4<false>(a.x + lo + e);
-            if (m_one) m[0] = ld4<false>(a.m + lo + e);
+            if (x_one) x[0] = ld_group<VEC, false>(a.x + lo + e);
+            if (m_one) m[0] = ld_group<VEC, false>(a.m + lo + e);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                x[r] = x_one ? x[0] : ld4<NT>(xb + r * a.ld + e);
-                m[r] = m_one ? m[0] : ld4<NT>(mb + r * a.ld + e);
+                x[r] = x_one ? x[0] : ld_group<VEC, NT>(xb + r * a.ld + e);
+                m[r] = m_one ? m[0] : ld_group<VEC, NT>(mb + r * a.ld + e);
             }
             h = ld4<false>(a.h + lo + e);
             xs = ld4<false>(a.xs + lo + e);
@@ -873,8 +890,8 @@ __global__ void __launch_bounds__((64 * span_waves<KT, R, FEW>()), (span_occupan
         const bool lead = R * w + r == 0;   // uniform
         const bool x_out = lead || !sp.merged_out, m_out = lead || !(sp.merged_out && p.avg_m);
         if (whole) {
-            if (x_out) st4<NT>(xb + r * a.ld + e, x[r]);
-            if (m_out) st4<NT>(mb + r * a.ld + e, m[r]);
+            if (x_out) st_group<VEC, NT>(xb + r * a.ld + e, x[r]);
+            if (m_out) st_group<VEC, NT>(mb + r * a.ld + e, m[r]);
         } else {
             if (x_out) { if (full) st4<NT>(xb + r * a.ld + e, x[r]); else st4_left(xb + r * a.ld + e, x[r], left); }
             if (m_out) { if (full) st4<NT>(mb + r * a.ld + e, m[r]); else st4_left(mb + r * a.ld + e, m[r], left); }

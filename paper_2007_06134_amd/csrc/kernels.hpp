@@ -133,7 +133,8 @@ hipError_t launch_average(const SyncParams &p, int64_t n_tiles, bool avg_m, bool
 // Workers whose replicas k_span and k_average hold in the registers of one block.
 constexpr int kMaxRegisterK = 128;
 constexpr int kSimds = 1024;   // of the 256 CUs
-// The span p.when.  With K above kMaxRegisterK a span that the device ends has
+// The span p.when; vec as for launch_local_step, but whole chunks of unaligned rows move
+// with dwordx4 too.  With K above kMaxRegisterK a span that the device ends has
 // n = 1; a planned one goes out as plain steps (step_nt, shape as for
 // launch_local_step) and one loop kernel per measured step.
 bool span_in_registers(int K);

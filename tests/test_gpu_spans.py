@@ -93,6 +93,21 @@ def test_unaligned_and_cut_rows(A, K, pad):
     assert list(recs["t"]) == syncs and np.allclose(v, var, rtol=1e-12, atol=0.0)
 
 
+# rows that start 4, 8 and 12 bytes behind a 16-byte boundary: whole chunks move with
+# four-byte aligned vectors, in every layout, and leave the neighbouring rows alone
+@pytest.mark.parametrize("P", [2305, 2306, 2307, 140_001])
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 7, 8, 16, 25, 32, 48, 64, 100])
+def test_whole_chunks_of_unaligned_rows(A, K, P):
+    w = _w(K=K, sizes=(1024, P - 1029, 5), p_init=3, total_steps=40, avg_momentum=K % 2 == 0)
+    x, m, syncs, var = _by_hand(A, w, 10, False)
+    xp, mp, _, _ = _by_hand(A, w, 10, True)
+    assert np.array_equal(x, xp) and np.array_equal(m, mp)
+    with A.Adpsgd.from_workload(w, pad_rows=False) as eng:
+        recs, v, _ = eng.run(10)
+        assert np.array_equal(eng.x.cpu().numpy(), x) and np.array_equal(eng.m.cpu().numpy(), m)
+    assert list(recs["t"]) == syncs and np.allclose(v, var, rtol=1e-12, atol=0.0)
+
+
 # periods around the most steps (64) and measurements (16) of a launch; K = 129
 # steps one at a time where the device decides
 @pytest.mark.parametrize("traced", [False, True])
