@@ -1309,7 +1309,8 @@ __global__ void __launch_bounds__(kFinishThreads) k_reduce_finish(ReduceParams r
     }
 }
 
-// The decisions of a launch of several measurements, in step order (one thread).
+// The decisions of a launch of more than kSerialSlots measurements, in step order (one
+// thread).
 __global__ void __launch_bounds__(64) k_control(ReduceParams r) {
     if (threadIdx.x != 0) return;
     SchedState st = *r.sched;
